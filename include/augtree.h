@@ -47,7 +47,9 @@
  *   on `stream` (the host staging happens before the call returns); smaller
  *   schedules travel in the kernel arguments. The backward also keeps
  *   D = rowsum(dO * O) of every row there (written by its dQ kernel, read by
- *   its dK/dV kernel).
+ *   its dK/dV kernel), and the fp32 partial sums of key tiles whose sweep is
+ *   split (trees with few key tiles and long sweeps; a second kernel of the
+ *   dK/dV launch adds them).
  * Errors: every call returns an augtree_status. Arguments are validated on
  *   the host before any work is enqueued; on error nothing is launched and
  *   augtree_last_error() gives a detail string (thread-local). No C++
@@ -55,8 +57,9 @@
  *   caller's next synchronisation, as in HIP.
  * Determinism: every output is bitwise reproducible run to run (no atomics),
  *   and a tree's outputs do not depend on the other trees of the batch (each
- *   output element is computed by one workgroup in a fixed order, whatever
- *   order the tiles are scheduled in).
+ *   output element is computed by one workgroup in a fixed order, or as parts
+ *   whose cuts follow from the tree alone and which are added in a fixed
+ *   order, whatever order the tiles are scheduled in).
  * Thread safety: calls are reentrant; calls on different streams that share a
  *   workspace race.
  */
@@ -293,8 +296,9 @@ int augtree_tree_bwd(const augtree_groups* grp, const uint16_t* q_p, const uint1
  * allocate device memory (code under stream capture, tight serving loops,
  * harnesses that forbid allocation). Same inputs, outputs and results as
  * augtree_tree_bwd (bit for bit: same kernels and schedule, except that a
- * batch whose chunked schedule does not fit the array runs one sweep per
- * prompt-key tile: the same prompt gradient up to fp32 summation order). Its
+ * batch whose split or chunked schedule does not fit the array runs without
+ * the splits, and if need be with one sweep per prompt-key tile: the same
+ * gradients up to fp32 summation order). Its
  * workspace is
  * a fixed 64 MiB device array of the library (augtree_noalloc_scratch_bytes()),
  * one copy per GPU, held from the first call on that GPU until the process

@@ -292,6 +292,22 @@ constexpr int KV_BQ = kDkvBlockQ;  // query rows per block (32 per wavefront of 
 constexpr int DKV_SDP_DEPTH = 3;  // LDS operand reads of S / dP run this many MFMAs ahead
 constexpr int DKV_DVK_DEPTH = 2;  // the same for the dV / dK transpose reads
 
+// Workgroup unit `i` of a launch: its item, or the whole tile i.
+__device__ __forceinline__ KVItem load_item(const DkvParams& p, int i) {
+  KVItem r{i, 0};
+  if (p.n_items > 0) {
+    if (p.items) {
+      r = p.items[i];
+    } else {
+      const uint32_t w = p.inl_items[i];
+      r = KVItem{(int32_t)(w >> 27), w & 0x7ffffffu};
+    }
+  }
+  r.tile = __builtin_amdgcn_readfirstlane(r.tile);
+  r.code = __builtin_amdgcn_readfirstlane(r.code);
+  return r;
+}
+
 template <int D>
 __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   // the workgroup's K and V tiles (operands of S = Q K^T and dP = dO V^T);
@@ -313,9 +329,11 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches below
   const int kq = wave_u & 3;   // 32-key slice of the tile
   const int qs = wave_u >> 2;  // 32-row half of every query block
-  const int tile_id = blockIdx.x / p.hkv;
-  const int kvh = blockIdx.x - tile_id * p.hkv;
-  const KVTile t = load_tile(p.tiles, p.inl, tile_id);
+  const int unit = blockIdx.x / p.hkv;
+  const int kvh = blockIdx.x - unit * p.hkv;
+  const KVItem it = load_item(p, unit);
+  const KVTile t = load_tile(p.tiles, p.inl, it.tile);
+  const int nparts = kv_item_nparts(it.code);
   const int pk = (t.flags & KV_PROMPT_KEYS) ? 1 : 0;  // prompt keys or branch keys
   const bool x_causal = (t.flags & KV_X_CAUSAL) != 0;
   const int kw0 = kq * 32;
@@ -340,7 +358,12 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   const int nxb = (t.x_len + KV_BQ - 1) / KV_BQ;
   const int nyb = (t.y_len + KV_BQ - 1) / KV_BQ;
   const int nxblk = p.group * nxb;
-  const int nblk = nxblk + p.group * nyb;
+  const int nall = nxblk + p.group * nyb;
+  // this workgroup's share of them, in sweep order
+  const int part = kv_item_part(it.code);
+  const int part_len = t.flags >> KV_PART_SHIFT;
+  const int blk0 = part * part_len;
+  const int nblk = part + 1 < nparts ? part_len : nall - blk0;
 
   // Query blocks in sweep order: (range, query head of the group, 64-row
   // block). Inside a range the blocks are swept from the end backwards and
@@ -375,27 +398,32 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   };
   // bytes from head g-1 to head 0 one block back
   const int64_t qback = ((int64_t)(g - 1) * D + KV_BQ * qstride) * 2;
-  // the last block of range y, head 0
-  auto range_start = [&](int y) {
+  // block `i` of range y in sweep order (0: the last block, head 0)
+  auto range_at = [&](int y, int i) {
     Cursor r;
     const int len = y ? t.y_len : t.x_len;
     const int64_t srow = y ? sry : srx;
     r.y = y;
-    r.hl = 0;
-    r.qb = (len + KV_BQ - 1) / KV_BQ - 1;
-    r.nvalid = len - r.qb * KV_BQ;
+    r.hl = i % g;
+    r.qb = (len + KV_BQ - 1) / KV_BQ - 1 - i / g;
+    r.nvalid = min(KV_BQ, len - r.qb * KV_BQ);
     r.nbytes = r.nvalid * qrow_bytes;
     r.sstep = srow * 4;
     r.sback = ((int64_t)(g - 1) * srow + KV_BQ) * 4;
     const int64_t row0 = (int64_t)(y ? t.kv_row0 : t.x_row0) + (int64_t)r.qb * KV_BQ;
-    const int64_t e0 = row0 * qstride + h0 * D;
+    const int64_t e0 = row0 * qstride + (h0 + r.hl) * D;
     r.qp = reinterpret_cast<const char*>(p.q[y] + e0);
     r.op = reinterpret_cast<const char*>(p.dout[y] + e0);
-    r.sp = reinterpret_cast<const char*>((y ? s_base1 : s_base0) + r.qb * KV_BQ);
+    r.sp = reinterpret_cast<const char*>((y ? s_base1 : s_base0) + r.qb * KV_BQ + r.hl * srow);
     return r;
   };
-  const Cursor ystart = range_start(1);
-  Cursor ld = nxb > 0 ? range_start(0) : ystart;
+  const Cursor ystart = range_at(1, 0);
+  Cursor ld = ystart;
+  if (part == 0) {  // (no divisions)
+    if (nxb > 0) ld = range_at(0, 0);
+  } else {
+    ld = blk0 < nxblk ? range_at(0, blk0) : range_at(1, blk0 - nxblk);
+  }
   // Step to the next block in sweep order (past the end of range Y: never
   // loaded). The pointers move by a step chosen on the (rare) head wrap and
   // range change paths and added on the one common path, so the compiler
@@ -570,6 +598,21 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   }
   if (qs != 0) return;
 
+  if (nparts > 1) {  // partial sums, in the accumulators' order (see dkv_combine_kernel)
+    float* const dst = p.part + ((int64_t)(kv_item_slot(it.code) + part) * p.hkv + kvh) * (2 * KV_BN * D);
+#pragma unroll
+    for (int ts = 0; ts < 2; ++ts)
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const f32x16& a = ts == 0 ? dk[db] : dv[db];
+          *reinterpret_cast<float4*>(dst + 4 * ((((ts * 4 + kq) * (D / 32) + db) * 4 + g4) * 64 + lane)) =
+              make_float4(a[g4 * 4 + 0], a[g4 * 4 + 1], a[g4 * 4 + 2], a[g4 * 4 + 3]);
+        }
+    return;
+  }
+
   // dK/dV tile: lane holds column d = 32*db + l32, rows = keys acc_row(i, hf)
   uint16_t* const dk16 = (t.flags & KV_OUT_BF16) ? p.dk[pk] : nullptr;
   uint16_t* const dv16 = (t.flags & KV_OUT_BF16) ? p.dv[pk] : nullptr;
@@ -598,6 +641,58 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   }
 }
 
+// Adds the partial sums of the split tiles in part order and writes the tile's
+// outputs, as the dK/dV kernel does for an unsplit tile. One thread adds four
+// consecutive accumulator registers of one lane: the four keys
+// 32 kq + acc_row(4 g4 .. 4 g4 + 3, hf) of column 32 db + l32. Bound by HBM:
+// 92 MB read and written in 18 us (5.2 TB/s). (Adding them in the part that
+// finishes last, found with a counter, instead: the device-scope fences write
+// back and invalidate the XCD's L2 under the running parts, and the dK/dV
+// launch of three small trees took 189 us against 131 us for both kernels.)
+constexpr int COMBINE_THREADS = 256;
+
+template <int D>
+__global__ __launch_bounds__(COMBINE_THREADS) void dkv_combine_kernel(DkvParams p) {
+  constexpr int PER_TILE = 2 * KV_BN * D / (4 * COMBINE_THREADS);  // workgroups per tile and KV head
+  const int u = blockIdx.x / PER_TILE;
+  const int e = u / p.hkv, kvh = u - e * p.hkv;
+  KVItem it;
+  if (p.combine) {
+    it = p.combine[e];
+  } else {
+    const uint32_t w = p.inl_combine[e];
+    it = KVItem{(int32_t)(w >> 27), w & 0x7ffffffu};
+  }
+  it.tile = __builtin_amdgcn_readfirstlane(it.tile);
+  it.code = __builtin_amdgcn_readfirstlane(it.code);
+  const KVTile t = load_tile(p.tiles, p.inl, it.tile);
+  const int nparts = kv_item_nparts(it.code);
+  const int f = (blockIdx.x - u * PER_TILE) * COMBINE_THREADS + threadIdx.x;
+  const int64_t slot_elems = (int64_t)p.hkv * (2 * KV_BN * D);
+  const float* src =
+      p.part + (int64_t)kv_item_slot(it.code) * slot_elems + (int64_t)kvh * (2 * KV_BN * D) + 4 * (int64_t)f;
+  f32x4 a = *reinterpret_cast<const f32x4*>(src);
+  for (int k = 1; k < nparts; ++k) a += *reinterpret_cast<const f32x4*>(src + k * slot_elems);
+
+  const int lane = f & 63, l32 = lane & 31, hf = lane >> 5;
+  const int g4 = (f >> 6) & 3, db = (f >> 8) % (D / 32), sl = (f >> 8) / (D / 32);
+  const int kq = sl & 3, ts = sl >> 2;
+  if (ts == 0) a *= p.scale;
+  const int pk = (t.flags & KV_PROMPT_KEYS) ? 1 : 0;
+  const int64_t kvstride = (int64_t)p.hkv * D;
+  const int64_t col = kvh * D + db * 32 + l32;
+  uint16_t* const o16 = (t.flags & KV_OUT_BF16) ? (ts ? p.dv[pk] : p.dk[pk]) : nullptr;
+  float* const o32 = (t.flags & KV_OUT_SLAB) ? p.slab + (ts * p.slab_rows + t.out_row0) * kvstride : nullptr;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int key = kq * 32 + g4 * 8 + hf * 4 + i;
+    if (key < t.kv_len) {
+      if (o32) o32[(int64_t)key * kvstride + col] = a[i];
+      if (o16) reinterpret_cast<__bf16*>(o16)[((int64_t)t.kv_row0 + key) * kvstride + col] = (__bf16)a[i];
+    }
+  }
+}
+
 }  // namespace
 
 hipError_t launch_attn_dq(const DqParams& p0, int n_tiles, hipStream_t stream) {
@@ -612,9 +707,15 @@ hipError_t launch_attn_dq(const DqParams& p0, int n_tiles, hipStream_t stream) {
 
 hipError_t launch_attn_dkv(const DkvParams& p, int n_tiles, hipStream_t stream) {
   if (n_tiles == 0) return hipSuccess;
-  const dim3 grid((unsigned)n_tiles * (unsigned)p.hkv), block(512);
+  const dim3 grid((unsigned)(p.n_items > 0 ? p.n_items : n_tiles) * (unsigned)p.hkv), block(512);
   if (p.head_dim == 128) hipLaunchKernelGGL((attn_dkv_kernel<128>), grid, block, 0, stream, p);
   else hipLaunchKernelGGL((attn_dkv_kernel<64>), grid, block, 0, stream, p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || p.n_combine == 0) return e;
+  const unsigned per_tile = (unsigned)(dkv_part_elems(p.head_dim) / (4 * COMBINE_THREADS));
+  const dim3 cgrid((unsigned)p.n_combine * (unsigned)p.hkv * per_tile), cblock(COMBINE_THREADS);
+  if (p.head_dim == 128) hipLaunchKernelGGL((dkv_combine_kernel<128>), cgrid, cblock, 0, stream, p);
+  else hipLaunchKernelGGL((dkv_combine_kernel<64>), cgrid, cblock, 0, stream, p);
   return hipGetLastError();
 }
 

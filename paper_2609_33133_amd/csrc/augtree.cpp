@@ -151,8 +151,12 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-int64_t qtile_cost(const QTile& t) { return (int64_t)t.q_len * (t.a_len + t.b_len); }
-int64_t kvtile_cost(const KVTile& t) { return (int64_t)(t.x_len + t.y_len) * t.kv_len; }
+// A tile's run time is its number of block steps: a tile with few valid rows
+// or keys sweeps as long as a full one. (Weighting by the valid rows started
+// the ragged tiles of long sweeps last: on a batch of four uneven trees the
+// dK/dV launch ended 17 % after the chip's average load, now 2 %.)
+int64_t qtile_cost(const QTile& t) { return cdiv(t.a_len, kFwdBlockN) + cdiv(t.b_len, kFwdBlockN); }
+int64_t kvtile_cost(const KVTile& t) { return cdiv(t.x_len, kDkvBlockQ) + cdiv(t.y_len, kDkvBlockQ); }
 
 // Tile order. Each XCD runs the tiles of one KV head in list order, so
 // concurrent workgroups share a K/V or Q/dO block in the XCD's L2 only when
@@ -169,7 +173,7 @@ int64_t kvtile_cost(const KVTile& t) { return (int64_t)(t.x_len + t.y_len) * t.k
 // segment, i.e. keeps the plain heaviest-first order: there the tail of a
 // late heavy tile costs more than the shared reads save.
 template <class T, class F>
-void sort_segment_major(std::vector<T>& v, const std::vector<int>& seg, F cost, int conc) {
+void sort_segment_major(std::vector<T>& v, std::vector<int>& seg, F cost, int conc) {
   int nseg = 0;
   for (int x : seg) nseg = std::max(nseg, x + 1);
   std::vector<int64_t> total(nseg, 0), top(nseg, 0);
@@ -202,8 +206,13 @@ void sort_segment_major(std::vector<T>& v, const std::vector<int>& seg, F cost, 
   }
   std::sort(key.begin(), key.end());
   std::vector<T> out(v.size());
-  for (size_t i = 0; i < v.size(); ++i) out[i] = v[std::get<3>(key[i])];
+  std::vector<int> out_seg(v.size());
+  for (size_t i = 0; i < v.size(); ++i) {
+    out[i] = v[std::get<3>(key[i])];
+    out_seg[i] = seg[std::get<3>(key[i])];
+  }
   v.swap(out);
+  seg.swap(out_seg);
 }
 
 // Tiles the chip runs at once (256 CUs of MI355X; a scheduling estimate, not
@@ -368,6 +377,51 @@ void add_response_kvtiles(TileList<KVTile>& L, const Shape& s, int bn) {
 // rows in L2.
 std::atomic<int> g_tree_chunk_blocks{kTreeChunkBlocksDefault};
 
+// Split of long dK/dV sweeps. A key tile is one workgroup per KV head and
+// its sweep is serial, so a tree with few key tiles and long sweeps (a short
+// prompt with many response rows, few KV heads) leaves most of the chip idle
+// behind its prompt tiles. Such a tile's sweep is cut into parts, which a
+// second kernel adds in part order. The rule reads the tile's own tree alone,
+// so that a tree's results do not depend on the batch: with `load` the tree's
+// block steps over the chip's 256 workgroup slots, its tiles are cut into
+// parts of max(load, kSplitMinBlocks) blocks if its longest sweep is at least
+// kSplitRatio times that. Measured (dK/dV launch and the addition): three
+// trees of P = 384 .. 1337 with 8 query and 2 KV heads, load 7 .. 25 blocks,
+// sweeps up to 352: 473 us unsplit, 131 us with parts of 32, 163 with 64, 146
+// with 16; one tree of P = 1500 with 16 / 4 heads (d = 64), load 105: 454
+// against 171 us. A part costs about 12 us of one workgroup slot (its
+// prologue and its 128 KB of partial sums written and read again), which is
+// lost where the batch's other trees fill the chip: four trees of P = 233 ..
+// 1811 with 32 / 8 heads, 463 us unsplit and 492 split, though their sweeps
+// are 2.3 .. 5.4 times their own loads. kSplitRatio leaves the nearly balanced
+// trees alone: a causal sequence of 4096 with 8 KV heads (1.94 times the
+// load) together with one of 1025 takes 337 us split and 395 unsplit, six of
+// 333 .. 4096 together 658 split and 630 unsplit.
+constexpr int kSplitMinBlocks = 32;
+constexpr double kSplitRatio = 1.75;
+
+int64_t q_blocks(int64_t rows) { return cdiv(rows, kDkvBlockQ); }
+
+// blocks per part for the tiles of tree g (0: not split)
+int64_t split_blocks(const Shape& s, int g, int bn) {
+  const int P = s.cp[g + 1] - s.cp[g];
+  const int64_t nr = s.nb > 0 ? s.cr[s.cb[g + 1]] - s.cr[s.cb[g]] : 0;
+  int64_t all = 0;
+  for (int k0 = 0; k0 < P; k0 += bn) all += q_blocks(nr) + q_blocks(P - k0);
+  if (s.nb > 0)
+    for (int b = s.cb[g]; b < s.cb[g + 1]; ++b)
+      for (int k0 = 0, R = s.cr[b + 1] - s.cr[b]; k0 < R; k0 += bn) all += q_blocks(R - k0);
+  const int64_t longest = (q_blocks(nr) + q_blocks(P)) * s.group;
+  const int64_t per = std::max<int64_t>(kSplitMinBlocks, all * s.group * s.hkv / 256);
+  if ((double)longest < kSplitRatio * (double)per) return 0;
+  return std::max<int64_t>(per, cdiv(longest, kMaxParts));
+}
+
+// parts of per_part blocks, the last one 0.5 .. 1.5 times as long
+int split_parts(int64_t blocks, int64_t per_part) {
+  return per_part == 0 ? 1 : (int)std::max<int64_t>(1, (blocks + per_part / 2) / per_part);
+}
+
 // Boundaries of chunk c of n of a group's `nr` response rows, on multiples of
 // the query block where possible.
 int seed_edge(int64_t nr, int k, int n, int bq) {
@@ -400,11 +454,60 @@ struct Plan {
   int64_t slab_rows = 0;
   std::vector<int32_t> row_map;
   size_t off_row_map = 0, off_slab = 0;
+  // split sweeps of the key tiles (none: empty): the launch's workgroups, the
+  // split tiles, and the fp32 scratch of their parts
+  std::vector<KVItem> items, combine;
+  int64_t slots = 0;
+  size_t off_items = 0, off_combine = 0, off_part = 0;
   std::vector<char> blob;
 
   void sort(const Shape& s) {
     for (auto& l : q) sort_segment_major(l.v, l.seg, qtile_cost, conc_qtiles(s));
     sort_segment_major(kv.v, kv.seg, kvtile_cost, conc_kvtiles(s));
+  }
+  // cut the sorted key tiles' long sweeps (after sort())
+  void split(const Shape& s, int bn) {
+    const size_t n = kv.v.size();
+    if (n == 0) return;
+    std::vector<int64_t> per(s.ng);
+    bool any = false;
+    for (int g = 0; g < s.ng; ++g) {
+      per[g] = split_blocks(s, g, bn);
+      any = any || per[g] > 0;
+    }
+    if (!any) return;
+    std::vector<int> tree(s.nb);
+    for (int g = 0; g < s.ng && s.nb > 0; ++g)
+      for (int b = s.cb[g]; b < s.cb[g + 1]; ++b) tree[b] = g;
+    std::vector<int> np(n, 1), slot0(n, 0);
+    for (size_t i = 0; i < n; ++i) {
+      const int g = kv.seg[i] < s.ng ? kv.seg[i] : tree[kv.seg[i] - s.ng];
+      np[i] = split_parts(kvtile_cost(kv.v[i]) * s.group, per[g]);
+      if (np[i] == 1) continue;
+      if (slots + np[i] >= (1 << 24) || per[g] >= (1 << 23)) {  // the code's and the flags' bits
+        np[i] = 1;
+        continue;
+      }
+      kv.v[i].flags |= (int32_t)per[g] << KV_PART_SHIFT;
+      slot0[i] = (int)slots;
+      slots += np[i];
+      combine.push_back({(int32_t)i, kv_item_code(slot0[i], 0, np[i])});
+    }
+    if (combine.empty()) return;
+    // the parts in the order of the tiles (by segment or heaviest first);
+    // equally long ones part by part, so that the workgroups that run
+    // together sweep the same query rows
+    std::vector<int> item_seg;
+    for (int k = 0; k < kMaxParts; ++k)
+      for (size_t i = 0; i < n; ++i)
+        if (k < np[i]) {
+          items.push_back({(int32_t)i, kv_item_code(slot0[i], k, np[i])});
+          item_seg.push_back(kv.seg[i]);
+        }
+    sort_segment_major(items, item_seg, [&](const KVItem& it) {
+      const int64_t all = kvtile_cost(kv.v[it.tile]) * s.group, per = kv.v[it.tile].flags >> KV_PART_SHIFT;
+      return kv_item_part(it.code) + 1 < kv_item_nparts(it.code) ? per : all - per * kv_item_part(it.code);
+    }, conc_kvtiles(s));
   }
   // every list gets room in the workspace (its size does not depend on
   // which lists end up inline)
@@ -416,6 +519,10 @@ struct Plan {
     }
     off_kv = o;
     o = align_up(o + kv.v.size() * sizeof(KVTile));
+    off_items = o;
+    o = align_up(o + items.size() * sizeof(KVItem));
+    off_combine = o;
+    o = align_up(o + combine.size() * sizeof(KVItem));
     off_row_map = o;
     o = align_up(o + row_map.size() * sizeof(int32_t));
     blob_bytes = o;
@@ -425,6 +532,8 @@ struct Plan {
     o = align_up(o + (size_t)dsum_rows_r * hq * sizeof(float));
     off_slab = o;
     o = align_up(o + (size_t)slab_rows * 2 * row_elems * sizeof(float));
+    off_part = o;
+    o = align_up(o + (size_t)slots * 2 * kDkvBlockN * row_elems * sizeof(float));
     bytes = std::max<size_t>(o, kAlign);
   }
   static bool inline_list(size_t n) { return n <= (size_t)kInlineTiles; }
@@ -433,7 +542,10 @@ struct Plan {
     size_t end = 0;
     for (int i = 0; i < 3; ++i)
       if (!inline_list(q[i].v.size())) end = off_q[i] + q[i].v.size() * sizeof(QTile);
-    if (!inline_list(kv.v.size())) end = off_kv + kv.v.size() * sizeof(KVTile);
+    if (!inline_list(kv.v.size())) {
+      end = off_kv + kv.v.size() * sizeof(KVTile);
+      if (!combine.empty()) end = off_combine + combine.size() * sizeof(KVItem);
+    }
     if (!row_map.empty()) end = off_row_map + row_map.size() * sizeof(int32_t);
     return end;
   }
@@ -442,7 +554,13 @@ struct Plan {
     for (int i = 0; i < 3; ++i)
       if (!inline_list(q[i].v.size()))
         std::memcpy(blob.data() + off_q[i], q[i].v.data(), q[i].v.size() * sizeof(QTile));
-    if (!inline_list(kv.v.size())) std::memcpy(blob.data() + off_kv, kv.v.data(), kv.v.size() * sizeof(KVTile));
+    if (!inline_list(kv.v.size())) {
+      std::memcpy(blob.data() + off_kv, kv.v.data(), kv.v.size() * sizeof(KVTile));
+      if (!combine.empty()) {
+        std::memcpy(blob.data() + off_items, items.data(), items.size() * sizeof(KVItem));
+        std::memcpy(blob.data() + off_combine, combine.data(), combine.size() * sizeof(KVItem));
+      }
+    }
     if (!row_map.empty()) std::memcpy(blob.data() + off_row_map, row_map.data(), row_map.size() * sizeof(int32_t));
   }
 };
@@ -456,6 +574,23 @@ void bind_tiles(P& p, const TileList<T>& L, void* ws, size_t off) {
     std::copy(L.v.begin(), L.v.end(), p.inl);
   } else {
     p.tiles = reinterpret_cast<const T*>(static_cast<char*>(ws) + off);
+  }
+}
+
+// The same for the items of a launch with split sweeps.
+void bind_split(DkvParams& p, const Plan& pl, void* ws) {
+  if (pl.combine.empty()) return;
+  char* const base = static_cast<char*>(ws);
+  p.n_items = (int)pl.items.size();
+  p.n_combine = (int)pl.combine.size();
+  p.part = reinterpret_cast<float*>(base + pl.off_part);
+  if (Plan::inline_list(pl.kv.v.size())) {
+    auto word = [](const KVItem& it) { return (uint32_t)it.tile << 27 | it.code; };
+    std::transform(pl.items.begin(), pl.items.end(), p.inl_items, word);
+    std::transform(pl.combine.begin(), pl.combine.end(), p.inl_combine, word);
+  } else {
+    p.items = reinterpret_cast<const KVItem*>(base + pl.off_items);
+    p.combine = reinterpret_cast<const KVItem*>(base + pl.off_combine);
   }
 }
 
@@ -500,7 +635,8 @@ Plan plan_for(const Shape& s, int op, int arg) {
       break;
     case AUGTREE_OP_TREE_BWD: {
       // arg bit 0: the fp32 copy of the prompt-key gradient is requested too;
-      // bit 1: no chunked prompt-key sweeps (keeps the workspace small)
+      // bit 1: no chunked prompt-key sweeps, bit 2: no split sweeps (both keep
+      // the workspace small)
       add_prefill_qtiles(pl.q[0], s, dq_block_m());
       add_replay_qtiles(pl.q[0], s, dq_block_m(), RP_FUSED);
       add_response_kvtiles(pl.kv, s, bn);
@@ -547,6 +683,7 @@ Plan plan_for(const Shape& s, int op, int arg) {
       break;
   }
   pl.sort(s);
+  if (!(op == AUGTREE_OP_TREE_BWD && (arg & 4))) pl.split(s, bn);
   pl.layout(s.hq, (int64_t)s.hkv * s.d);
   return pl;
 }
@@ -663,6 +800,7 @@ int run_bwd(const Shape& s, const Plan& pl, const Tensors& x, const BwdOut& out,
   if (!pl.kv.v.empty()) {
     DkvParams p{};
     bind_tiles(p, pl.kv, ws, pl.off_kv);
+    bind_split(p, pl, ws);
     p.k[0] = x.k_r; p.v[0] = x.v_r; p.k[1] = x.k_p; p.v[1] = x.v_p;
     p.q[0] = x.q_r; p.q[1] = x.q_p;
     p.dout[0] = x.do_r; p.dout[1] = x.do_p;
@@ -913,9 +1051,12 @@ int tree_bwd_impl(const augtree_groups* grp, const uint16_t* q_p, const uint16_t
   OPTIONAL_PTR(dkv_p_f32);
   Plan pl = plan_for(s, AUGTREE_OP_TREE_BWD, dkv_p_f32 ? 1 : 0);
   if (scratch) {  // the caller's buffer is a fixed device array: check its size before touching the device
-    // chunked prompt-key sweeps need an fp32 slab; without room for it, one
-    // sweep per prompt key tile (the same sum in another fp32 order)
-    if (pl.bytes > ws_bytes && pl.n_parts > 0) pl = plan_for(s, AUGTREE_OP_TREE_BWD, (dkv_p_f32 ? 1 : 0) | 2);
+    // split and chunked sweeps need fp32 partial sums; without room for them,
+    // first no splits, then one sweep per key tile (the same sums in another
+    // fp32 order)
+    const int arg = dkv_p_f32 ? 1 : 0;
+    if (pl.bytes > ws_bytes && pl.slots > 0) pl = plan_for(s, AUGTREE_OP_TREE_BWD, arg | 4);
+    if (pl.bytes > ws_bytes && pl.n_parts > 0) pl = plan_for(s, AUGTREE_OP_TREE_BWD, arg | 6);
     if (pl.bytes > ws_bytes)
       return fail(AUGTREE_ERR_WORKSPACE,
                   "this batch needs %zu bytes of scratch; the allocation-free entry point holds at most %zu bytes",

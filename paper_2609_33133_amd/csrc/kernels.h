@@ -69,8 +69,20 @@ struct DkvParams {
   int64_t slab_rows;
   int hq, hkv, group, head_dim;
   float scale, scale_log2;
+  // split sweeps (n_items > 0): the launch's workgroups, the tiles whose
+  // parts have to be added (code: first slot, part 0, nparts) and the fp32
+  // scratch of the partial sums, [slots][hkv][2][128 x d]
+  const KVItem* items;        // device, or nullptr: `inl_items`
+  const KVItem* combine;      // device, or nullptr: `inl_combine`
+  int n_items, n_combine;
+  float* part;
   KVTile inl[kInlineTiles];
+  uint32_t inl_items[kInlineTiles * kMaxParts];
+  uint32_t inl_combine[kInlineTiles];
 };
+
+// fp32 values of one scratch slot and KV head (dK and dV of a 128-key tile)
+inline int64_t dkv_part_elems(int head_dim) { return 2 * (int64_t)kDkvBlockN * head_dim; }
 
 hipError_t launch_attn_fwd(const FwdParams& p, int n_tiles, bool out_f32, hipStream_t stream);
 hipError_t launch_attn_dq(const DqParams& p, int n_tiles, hipStream_t stream);

@@ -3,6 +3,11 @@
 
 #include <stdint.h>
 
+#if !defined(__host__)  // plain C++ (the host library)
+#define __host__
+#define __device__
+#endif
+
 namespace augtree {
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -61,6 +66,31 @@ enum : int32_t {
   KV_X_CAUSAL = 2,
   KV_OUT_BF16 = 4,
   KV_OUT_SLAB = 8,
+  KV_PART_SHIFT = 8,  // flags >> KV_PART_SHIFT: blocks of a part (split tiles)
 };
+
+// One workgroup of a dK/dV launch whose long sweeps are split: part `part` of
+// `nparts` of tile `tile`'s query blocks in sweep order. The parts are
+// flags >> KV_PART_SHIFT blocks long, the last one takes the rest (the same
+// cuts for every tile of a segment, so that parts that run together read the
+// same query rows). A tile with nparts = 1 writes its outputs; the parts of a
+// split tile write fp32 partial sums to the consecutive scratch slots
+// slot0 + part, which a combine kernel adds in part order. code = slot0 << 8 |
+// part << 4 | (nparts - 1). A launch whose tiles travel in the kernel
+// arguments (at most 32) carries its items there as one word each: tile <<
+// 27 | code (slot0 < 512).
+struct KVItem {
+  int32_t tile;
+  uint32_t code;
+};
+
+constexpr int kMaxParts = 16;  // parts of one tile (4 bits of the code)
+
+__host__ __device__ inline uint32_t kv_item_code(int slot, int part, int nparts) {
+  return (uint32_t)slot << 8 | (uint32_t)part << 4 | (uint32_t)(nparts - 1);
+}
+__host__ __device__ inline int kv_item_slot(uint32_t code) { return (int)(code >> 8); }
+__host__ __device__ inline int kv_item_part(uint32_t code) { return (int)(code >> 4) & 15; }
+__host__ __device__ inline int kv_item_nparts(uint32_t code) { return (int)(code & 15) + 1; }
 
 }  // namespace augtree

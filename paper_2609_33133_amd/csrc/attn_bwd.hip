@@ -5,7 +5,7 @@
 //
 // Two kernels, no atomics, every output written once:
 // * attn_dq_kernel (query-outer): one workgroup (4 wavefronts, two workgroups
-//   per CU) per 128-row query tile and query head, sweeping the same key
+//   per CU) per 128 (query row, head) pairs of one KV head (QRows), sweeping the same key
 //   segments as the forward (prompt keys, then the branch's own causal keys)
 //   in 64-key blocks, each handled as two 32-key halves. S^T, dP^T and dS^T
 //   keep one query per lane; dQ^T += K^T dS^T takes dS^T straight from the
@@ -37,20 +37,25 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   __shared__ __bf16 k_buf0[DQ_BN * D], k_buf1[DQ_BN * D], v_buf0[DQ_BN * D], v_buf1[DQ_BN * D];
   int unit, hh;
   if (!xcd_unit(p.n_units, p.group, unit, hh)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = tid >> 6;
   const int tile_id = unit / p.hkv;
   const int kvh = unit - tile_id * p.hkv;
-  const int head = kvh * p.group + hh;
   const QTile t = load_tile(p.tiles, p.inl, tile_id);
+  const QRows rows(t, p.group, hh, wave, l32);
+  if (!rows.any) return;
   const bool prow = (t.flags & QT_PROMPT_ROWS) != 0;  // prompt rows (prefill) or response rows
   const uint16_t* const kb = prow ? p.kb[1] : p.kb[0];
   const uint16_t* const vb = prow ? p.vb[1] : p.vb[0];
   const int64_t lrows = prow ? p.lse_rows[1] : p.lse_rows[0];
-  const int qi = wave * 32 + l32;
-  const bool qvalid = qi < t.q_len;
-  const int64_t qrow = (int64_t)t.q_row0 + qi;
+  const int qi = rows.row;
   const int64_t qstride = (int64_t)p.hq * D;
   const int64_t kvstride = (int64_t)p.hkv * D;
+  // this lane's elements in Q / dO / O / dQ (uniform start, 32-bit offset) and
+  // its LSE and D
+  const int64_t qbase = t.q_row0 * qstride + (int64_t)kvh * p.group * D;
+  const int qoff = qi * (int)qstride + rows.head * D;
+  const int64_t srow = (int64_t)(kvh * p.group + rows.head) * lrows + t.q_row0 + qi;
 
   // Q^T and dO^T operands: lane holds query qi, d = 16*ks + 8*hf .. +7.
   // D = rowsum(dO * O) of the query is formed here from the same halves
@@ -59,17 +64,16 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   bf16x8 qreg[D / 16], doreg[D / 16];
   float dsq;
   {
-    const int64_t off = qrow * qstride + head * D + hf * 8;
-    const uint16_t* qs = (prow ? p.q[1] : p.q[0]) + off;
-    const uint16_t* ds = (prow ? p.dout[1] : p.dout[0]) + off;
-    const uint16_t* os = (prow ? p.o[1] : p.o[0]) + off;
+    const int off = qoff + hf * 8;
+    const uint16_t* qs = (prow ? p.q[1] : p.q[0]) + qbase + off;
+    const uint16_t* ds = (prow ? p.dout[1] : p.dout[0]) + qbase + off;
+    const uint16_t* os = (prow ? p.o[1] : p.o[0]) + qbase + off;
     float part[D / 16];
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
-      const uint4 z = make_uint4(0, 0, 0, 0);
-      qreg[ks] = as_bf16x8(qvalid ? ldg16(qs + ks * 16) : z);
-      const uint4 dv = qvalid ? ldg16(ds + ks * 16) : z;
-      const uint4 ov = qvalid ? ldg16(os + ks * 16) : z;
+      qreg[ks] = as_bf16x8(ldg16(qs + ks * 16));
+      const uint4 dv = ldg16(ds + ks * 16);
+      const uint4 ov = ldg16(os + ks * 16);
       doreg[ks] = as_bf16x8(dv);
       float a = 0.f;
 #pragma unroll
@@ -83,11 +87,10 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
       for (int ks = 0; ks < w; ++ks) part[ks] += part[ks + w];
     dsq = pair_sum(part[0]);
   }
-  if (qvalid && hf == 0) (prow ? p.dsum[1] : p.dsum[0])[(int64_t)head * lrows + qrow] = dsq;
+  if (rows.valid && hf == 0) (prow ? p.dsum[1] : p.dsum[0])[srow] = dsq;
   // S and dP accumulators start at -LSE / scale and -D of this lane's query,
   // so the MFMAs leave S - LSE / scale and dP - D: P = exp2(c * s), dS = P * dp
-  const float nlse = qvalid ? -(prow ? p.lse[1] : p.lse[0])[(int64_t)head * lrows + qrow] / p.scale : 0.f;
-  if (!qvalid) dsq = 0.f;
+  const float nlse = -(prow ? p.lse[1] : p.lse[0])[srow] / p.scale;
   const float c = p.scale_log2;
 
   f32x16 acc[D / 32];
@@ -100,7 +103,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   float ds_sum = 0.f;
 
   const int nA = (t.a_len + DQ_BN - 1) / DQ_BN;
-  const int nB = (t.b_len + DQ_BN - 1) / DQ_BN;
+  // segment B up to the workgroup's last row
+  const int nB = t.b_len > 0 ? (t.b_qpos + rows.last) / DQ_BN + 1 : 0;
   const int nblk = nA + nB;
 
   TileCopy<DQ_BN, D, 4> cp;
@@ -158,12 +162,12 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
     const bool isB = k.isB != 0;
     const int kb0 = k.kb0;
     const int len = k.len;
-    const int qpos_lo = t.b_qpos + wave * 32;
+    const int qpos_lo = t.b_qpos + rows.wlo, qpos_hi = t.b_qpos + rows.whi;
     const int qpos = t.b_qpos + qi;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       const int k0 = kb0 + half * 32;  // first key of this 32-key half
-      const bool skip = isB && (k0 > qpos_lo + 31);
+      const bool skip = !rows.wave_any || (isB && (k0 > qpos_hi));
       if (skip) continue;
       f32x16 s, dp;
 #pragma unroll
@@ -256,8 +260,10 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   // component shared by the keys no longer multiplies the rounding error.
   const float ds_tot = pair_sum(ds_sum);
   const float inv_n0 = 1.f / (float)min(DQ_BN, t.a_len > 0 ? t.a_len : t.b_len);
-  if (qvalid) {
-    const int64_t obase = qrow * qstride + head * D;
+  // (the lane's row again, instead of registers held over the sweep)
+  const QRows er(t, p.group, hh, wave, (int)opaque(l32));
+  if (er.valid) {
+    const int64_t eoff = qbase + er.row * (int)qstride + er.head * D;
     uint16_t* const dq16 = prow ? p.dq[1] : p.dq[0];
     float* const dq32 = prow ? p.dq32[1] : p.dq32[0];
 #pragma unroll
@@ -273,12 +279,12 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
         const float v1 = (acc[db][g4 * 4 + 1] - corr * cs[1]) * p.scale;
         const float v2 = (acc[db][g4 * 4 + 2] - corr * cs[2]) * p.scale;
         const float v3 = (acc[db][g4 * 4 + 3] - corr * cs[3]) * p.scale;
-        if (dq32) *reinterpret_cast<float4*>(dq32 + obase + dd) = make_float4(v0, v1, v2, v3);
+        if (dq32) *reinterpret_cast<float4*>(dq32 + eoff + dd) = make_float4(v0, v1, v2, v3);
         if (dq16) {
           typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
           bf16x4 w;
           w[0] = (__bf16)v0; w[1] = (__bf16)v1; w[2] = (__bf16)v2; w[3] = (__bf16)v3;
-          *reinterpret_cast<bf16x4*>(dq16 + obase + dd) = w;
+          *reinterpret_cast<bf16x4*>(dq16 + eoff + dd) = w;
         }
       }
     }

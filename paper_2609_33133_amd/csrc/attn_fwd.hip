@@ -1,9 +1,9 @@
 // Forward attention kernel for gfx950: prompt prefill, fused response replay
 // and the split-mode partials (§3.2, Eq. 1, §3.3).
 //
-// One workgroup = 4 wavefronts = one query tile of up to 128 rows of one
-// query head; each wavefront owns 32 query rows (one per lane column of the
-// S^T accumulator). The tile sweeps 64-key blocks of segment A (the prompt
+// One workgroup = 4 wavefronts = 128 (query row, head) pairs of one KV head
+// (QRows); each wavefront owns 32 of them (one per lane column of the S^T
+// accumulator). The workgroup sweeps 64-key blocks of segment A (the prompt
 // KV, every key visible) and then of segment B (causal). Continuing the
 // online softmax across the two segments is the log-sum-exp merge of the two
 // partial states done in registers; a tile with only one segment produces one
@@ -50,26 +50,29 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches below
   const int tile_id = unit / p.hkv;
   const int kvh = unit - tile_id * p.hkv;
-  const int head = kvh * p.group + hh;
   const QTile t = load_tile(p.tiles, p.inl, tile_id);
+  const QRows rows(t, p.group, hh, wave, l32);
+  if (!rows.any) return;
   // prompt rows (prefill) or response rows (replay): tensors of the tile
   const bool prow = (t.flags & QT_PROMPT_ROWS) != 0;
   const uint16_t* const qsrc = prow ? p.q[1] : p.q[0];
   const uint16_t* const kb = prow ? p.kb[1] : p.kb[0];
   const uint16_t* const vb = prow ? p.vb[1] : p.vb[0];
-  const int qi = wave * 32 + l32;
-  const bool qvalid = qi < t.q_len;
-  const int64_t qrow = (int64_t)t.q_row0 + qi;
+  const int qi = rows.row;
   const int64_t qstride = (int64_t)p.hq * D;
   const int64_t kvstride = (int64_t)p.hkv * D;
+  // this lane's elements in Q / O: uniform start of the tile's rows of KV
+  // head kvh, plus a 32-bit offset
+  const int64_t qbase = t.q_row0 * qstride + (int64_t)kvh * p.group * D;
+  const int qoff = qi * (int)qstride + rows.head * D;
 
   // Q^T operand (B of S^T = K Q^T): lane holds query qi, d = 16*ks + 8*hf .. +7
   bf16x8 qreg[D / 16];
   {
-    const uint16_t* qp = qsrc + qrow * qstride + head * D + hf * 8;
+    const uint16_t* qp = qsrc + qbase + qoff + hf * 8;
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks)
-      qreg[ks] = as_bf16x8(qvalid ? ldg16(qp + ks * 16) : make_uint4(0, 0, 0, 0));
+      qreg[ks] = as_bf16x8(ldg16(qp + ks * 16));
   }
 
   const float c = p.scale_log2;
@@ -82,7 +85,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
     for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
 
   const int nA = (t.a_len + BN - 1) / BN;
-  const int nB = (t.b_len + BN - 1) / BN;
+  // segment B up to the workgroup's last row
+  const int nB = t.b_len > 0 ? (t.b_qpos + rows.last) / BN + 1 : 0;
   const int nblk = nA + nB;
 
   TileCopy<BN, D, 4> cp;
@@ -123,11 +127,13 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   k_off.init(l32, hf);
   TrOffsets<D> vtr_off;  // V^T operands
   vtr_off.init(0, lane);
-  const int qpos_lo = t.b_qpos + wave * 32;  // causal: the wavefront's first query position
+  const int qpos_lo = t.b_qpos + rows.wlo;  // causal: the wavefront's first query position
 
   // a causal block whose keys all follow the wavefront's queries (and every
-  // later block) contributes nothing
-  auto skipped = [&](int b) { return b >= nA && (b - nA) * BN > qpos_lo + 31; };
+  // later block) contributes nothing; neither does any block to a wavefront
+  // without rows
+  const int nlive = !rows.wave_any ? 0 : t.b_len > 0 ? nA + (t.b_qpos + rows.whi) / BN + 1 : nA;
+  auto skipped = [&](int b) { return b >= nlive; };
 
   // S^T of one 64-key block (two 32-key halves), raw scores
   auto s_mfma = [&](const __bf16* kl, f32x16& s0, f32x16& s1) {
@@ -261,12 +267,14 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   }
 
   const float l_tot = pair_sum(l_run);
-  if (qvalid) {
+  // (the lane's row again, instead of registers held over the sweep)
+  const QRows er(t, p.group, hh, wave, (int)opaque(l32));
+  if (er.valid) {
+    const int eoff = er.row * (int)qstride + er.head * D;
     const float inv = 1.f / l_tot;
-    const int64_t obase = qrow * qstride + head * D;
     const bool part1 = (t.flags & QT_PART1) != 0;
-    float* const o32 = p.o32 + (part1 ? p.o32_part : 0);
-    uint16_t* const o16 = prow ? p.o[1] : p.o[0];
+    float* const o32 = p.o32 + (part1 ? p.o32_part : 0) + qbase;
+    uint16_t* const o16 = (prow ? p.o[1] : p.o[0]) + qbase;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) {
 #pragma unroll
@@ -275,12 +283,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
         const float v0 = oacc[db][g4 * 4 + 0] * inv, v1 = oacc[db][g4 * 4 + 1] * inv;
         const float v2 = oacc[db][g4 * 4 + 2] * inv, v3 = oacc[db][g4 * 4 + 3] * inv;
         if constexpr (OUT32) {
-          *reinterpret_cast<float4*>(o32 + obase + d0) = make_float4(v0, v1, v2, v3);
+          *reinterpret_cast<float4*>(o32 + eoff + d0) = make_float4(v0, v1, v2, v3);
         } else {
           typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
           bf16x4 w;
           w[0] = (__bf16)v0; w[1] = (__bf16)v1; w[2] = (__bf16)v2; w[3] = (__bf16)v3;
-          *reinterpret_cast<bf16x4*>(o16 + obase + d0) = w;
+          *reinterpret_cast<bf16x4*>(o16 + eoff + d0) = w;
         }
       }
     }
@@ -294,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
         lse = prow ? p.lse[1] : p.lse[0];
         lrows = prow ? p.lse_rows[1] : p.lse_rows[0];
       }
-      lse[(int64_t)head * lrows + qrow] = (m_run * c + __log2f(l_tot)) * kLn2;
+      lse[(int64_t)(kvh * p.group + er.head) * lrows + t.q_row0 + er.row] = (m_run * c + __log2f(l_tot)) * kLn2;
     }
   }
 }

@@ -36,13 +36,13 @@ template <int D>
 __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   __shared__ __bf16 k_buf0[DQ_BN * D], k_buf1[DQ_BN * D], v_buf0[DQ_BN * D], v_buf1[DQ_BN * D];
   int unit, hh;
-  if (!xcd_unit(p.n_units, p.group, unit, hh)) return;
+  if (!xcd_unit(p.n_units, p.group, p.group_magic, unit, hh)) return;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = tid >> 6;
-  const int tile_id = unit / p.hkv;
+  const int tile_id = fast_div(unit, p.hkv, p.hkv_magic);
   const int kvh = unit - tile_id * p.hkv;
   const QTile t = load_tile(p.tiles, p.inl, tile_id);
-  const QRows rows(t, p.group, hh, wave, l32);
+  const QRows rows(t, p.group, p.group_magic, hh, wave, l32);
   if (!rows.any) return;
   const bool prow = (t.flags & QT_PROMPT_ROWS) != 0;  // prompt rows (prefill) or response rows
   const uint16_t* const kb = prow ? p.kb[1] : p.kb[0];
@@ -56,51 +56,6 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   const int64_t qbase = t.q_row0 * qstride + (int64_t)kvh * p.group * D;
   const int qoff = qi * (int)qstride + rows.head * D;
   const int64_t srow = (int64_t)(kvh * p.group + rows.head) * lrows + t.q_row0 + qi;
-
-  // Q^T and dO^T operands: lane holds query qi, d = 16*ks + 8*hf .. +7.
-  // D = rowsum(dO * O) of the query is formed here from the same halves
-  // (eight partial sums, a tree, and the half-wave exchange) and stored for
-  // the dK/dV kernel.
-  bf16x8 qreg[D / 16], doreg[D / 16];
-  float dsq;
-  {
-    const int off = qoff + hf * 8;
-    const uint16_t* qs = (prow ? p.q[1] : p.q[0]) + qbase + off;
-    const uint16_t* ds = (prow ? p.dout[1] : p.dout[0]) + qbase + off;
-    const uint16_t* os = (prow ? p.o[1] : p.o[0]) + qbase + off;
-    float part[D / 16];
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      qreg[ks] = as_bf16x8(ldg16(qs + ks * 16));
-      const uint4 dv = ldg16(ds + ks * 16);
-      const uint4 ov = ldg16(os + ks * 16);
-      doreg[ks] = as_bf16x8(dv);
-      float a = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        a += __uint_as_float(half16(dv, e) << 16) * __uint_as_float(half16(ov, e) << 16);
-      part[ks] = a;
-    }
-#pragma unroll
-    for (int w = D / 32; w >= 1; w >>= 1)
-#pragma unroll
-      for (int ks = 0; ks < w; ++ks) part[ks] += part[ks + w];
-    dsq = pair_sum(part[0]);
-  }
-  if (rows.valid && hf == 0) (prow ? p.dsum[1] : p.dsum[0])[srow] = dsq;
-  // S and dP accumulators start at -LSE / scale and -D of this lane's query,
-  // so the MFMAs leave S - LSE / scale and dP - D: P = exp2(c * s), dS = P * dp
-  const float nlse = -(prow ? p.lse[1] : p.lse[0])[srow] / p.scale;
-  const float c = p.scale_log2;
-
-  f32x16 acc[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
-  // sum over the keys of dS as rounded to bf16 for the dQ MFMAs (this lane's
-  // 16 keys of every 32-key half); see the correction at the end
-  float ds_sum = 0.f;
 
   const int nA = (t.a_len + DQ_BN - 1) / DQ_BN;
   // segment B up to the workgroup's last row
@@ -152,6 +107,55 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
     kc.kp += dk;
     kc.vp += dv;
   };
+
+  // the first block's copy goes out before anything else is computed
+  Blk c0{0, 0, 0}, c1{0, 0, 0};
+  if (nblk > 0) load_next(k_buf0, v_buf0, c0);
+
+  // Q^T and dO^T operands: lane holds query qi, d = 16*ks + 8*hf .. +7.
+  // D = rowsum(dO * O) of the query is formed here from the same halves
+  // (eight partial sums, a tree, and the half-wave exchange) and stored for
+  // the dK/dV kernel.
+  bf16x8 qreg[D / 16], doreg[D / 16];
+  float dsq;
+  {
+    const int off = qoff + hf * 8;
+    const uint16_t* qs = (prow ? p.q[1] : p.q[0]) + qbase + off;
+    const uint16_t* ds = (prow ? p.dout[1] : p.dout[0]) + qbase + off;
+    const uint16_t* os = (prow ? p.o[1] : p.o[0]) + qbase + off;
+    float part[D / 16];
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+      qreg[ks] = as_bf16x8(ldg16(qs + ks * 16));
+      const uint4 dv = ldg16(ds + ks * 16);
+      const uint4 ov = ldg16(os + ks * 16);
+      doreg[ks] = as_bf16x8(dv);
+      float a = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        a += __uint_as_float(half16(dv, e) << 16) * __uint_as_float(half16(ov, e) << 16);
+      part[ks] = a;
+    }
+#pragma unroll
+    for (int w = D / 32; w >= 1; w >>= 1)
+#pragma unroll
+      for (int ks = 0; ks < w; ++ks) part[ks] += part[ks + w];
+    dsq = pair_sum(part[0]);
+  }
+  if (rows.valid && hf == 0) (prow ? p.dsum[1] : p.dsum[0])[srow] = dsq;
+  // S and dP accumulators start at -LSE / scale and -D of this lane's query,
+  // so the MFMAs leave S - LSE / scale and dP - D: P = exp2(c * s), dS = P * dp
+  const float nlse = -(prow ? p.lse[1] : p.lse[0])[srow] / p.scale;
+  const float c = p.scale_log2;
+
+  f32x16 acc[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+  // sum over the keys of dS as rounded to bf16 for the dQ MFMAs (this lane's
+  // 16 keys of every 32-key half); see the correction at the end
+  float ds_sum = 0.f;
 
   RowOffsets<D> r0_off, r1_off;  // K/V rows l32 and 32 + l32
   r0_off.init(l32, hf);
@@ -205,8 +209,6 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
     }
   };
 
-  Blk c0{0, 0, 0}, c1{0, 0, 0};
-  if (nblk > 0) load_next(k_buf0, v_buf0, c0);
   wait_vmem();
   __syncthreads();
   // The vector c of the common-mode correction at the end: the mean of the
@@ -260,35 +262,32 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   // component shared by the keys no longer multiplies the rounding error.
   const float ds_tot = pair_sum(ds_sum);
   const float inv_n0 = 1.f / (float)min(DQ_BN, t.a_len > 0 ? t.a_len : t.b_len);
-  // (the lane's row again, instead of registers held over the sweep)
-  const QRows er(t, p.group, hh, wave, (int)opaque(l32));
-  if (er.valid) {
-    const int64_t eoff = qbase + er.row * (int)qstride + er.head * D;
-    uint16_t* const dq16 = prow ? p.dq[1] : p.dq[0];
-    float* const dq32 = prow ? p.dq32[1] : p.dq32[0];
+  if (tid < D) kmean_part[0][tid] = ((kmean_part[0][tid] + kmean_part[1][tid]) + kmean_part[2][tid]) + kmean_part[3][tid];
+  __syncthreads();
+  if (!rows.wave_any) return;
+  const float corr = ds_tot * inv_n0;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
+  for (int db = 0; db < D / 32; ++db) {
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int dd = db * 32 + g4 * 8 + hf * 4;
-        f32x4 cs = *reinterpret_cast<const f32x4*>(&kmean_part[0][dd]);
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const f32x4 cs = *reinterpret_cast<const f32x4*>(&kmean_part[0][db * 32 + g4 * 8 + hf * 4]);
 #pragma unroll
-        for (int w = 1; w < 4; ++w) cs += *reinterpret_cast<const f32x4*>(&kmean_part[w][dd]);
-        const float corr = ds_tot * inv_n0;
-        const float v0 = (acc[db][g4 * 4 + 0] - corr * cs[0]) * p.scale;
-        const float v1 = (acc[db][g4 * 4 + 1] - corr * cs[1]) * p.scale;
-        const float v2 = (acc[db][g4 * 4 + 2] - corr * cs[2]) * p.scale;
-        const float v3 = (acc[db][g4 * 4 + 3] - corr * cs[3]) * p.scale;
-        if (dq32) *reinterpret_cast<float4*>(dq32 + eoff + dd) = make_float4(v0, v1, v2, v3);
-        if (dq16) {
-          typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-          bf16x4 w;
-          w[0] = (__bf16)v0; w[1] = (__bf16)v1; w[2] = (__bf16)v2; w[3] = (__bf16)v3;
-          *reinterpret_cast<bf16x4*>(dq16 + eoff + dd) = w;
-        }
-      }
+      for (int e = 0; e < 4; ++e) acc[db][g4 * 4 + e] -= corr * cs[e];
     }
   }
+  // through this wavefront's own buffer (nothing is in flight any more)
+  const int wv = __builtin_amdgcn_readfirstlane(wave);
+  // (an opaque lane: with the epilogue's addresses folded into the sweep's the
+  // compiler schedules the block loop 6 % slower)
+  const int el = (int)opaque(lane);
+  char* const buf = reinterpret_cast<char*>(wv == 0 ? k_buf0 : wv == 1 ? k_buf1 : wv == 2 ? v_buf0 : v_buf1);
+  uint16_t* const dq16 = prow ? p.dq[1] : p.dq[0];
+  float* const dq32 = prow ? p.dq32[1] : p.dq32[0];
+  if (dq32)
+    store_pairs<D>(buf, acc, p.scale, dq32 + qbase, qstride, t, p.group, p.group_magic, hh, wv, el);
+  if (dq16)
+    store_pairs<D>(buf, acc, p.scale, reinterpret_cast<__bf16*>(dq16) + qbase, qstride, t, p.group, p.group_magic, hh,
+                   wv, el);
 }
 
 // ----------------------------------------------------------------------------- dK/dV
@@ -297,6 +296,20 @@ constexpr int KV_BN = kDkvBlockN;  // keys per workgroup (32 per wavefront pair)
 constexpr int KV_BQ = kDkvBlockQ;  // query rows per block (32 per wavefront of a pair)
 constexpr int DKV_SDP_DEPTH = 3;  // LDS operand reads of S / dP run this many MFMAs ahead
 constexpr int DKV_DVK_DEPTH = 2;  // the same for the dV / dK transpose reads
+
+// Copies up to 32 rows of D elements from LDS (dense) to rows of `dst`, 16
+// bytes per lane.
+template <int D, class T>
+__device__ __forceinline__ void store_rows(const T* lds, T* dst, int64_t stride, int nrows, int lane) {
+  constexpr int CPR = D * sizeof(T) / 16, RPI = 64 / CPR;
+  const int ch = lane & (CPR - 1), r0 = lane / CPR;
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int r = r0 + i * RPI;
+    const raw16 v = reinterpret_cast<const raw16*>(lds + r * D)[ch];
+    if (r < nrows) reinterpret_cast<raw16*>(dst + r * stride)[ch] = v;
+  }
+}
 
 // Workgroup unit `i` of a launch: its item, or the whole tile i.
 __device__ __forceinline__ KVItem load_item(const DkvParams& p, int i) {
@@ -335,7 +348,7 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches below
   const int kq = wave_u & 3;   // 32-key slice of the tile
   const int qs = wave_u >> 2;  // 32-row half of every query block
-  const int unit = blockIdx.x / p.hkv;
+  const int unit = fast_div(blockIdx.x, p.hkv, p.hkv_magic);
   const int kvh = blockIdx.x - unit * p.hkv;
   const KVItem it = load_item(p, unit);
   const KVTile t = load_tile(p.tiles, p.inl, it.tile);
@@ -577,73 +590,76 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
     }
   }
 
-  // Add the partials of wavefronts w + 4 into w through LDS (the query-block
-  // buffers are free now; key slice kq uses one of the four), then wavefronts
-  // 0..3 write the tile. Accumulator register i of lane l sits at
-  // [db][i][lane] of the exchange buffer.
-  __bf16* xbuf = kq == 0 ? q_buf0 : kq == 1 ? q_buf1 : kq == 2 ? o_buf0 : o_buf1;
-  float* myx = reinterpret_cast<float*>(xbuf);
-  static_assert((D / 32) * 16 * 64 * 4 <= KV_BQ * D * 2, "exchange fits one query buffer");
+  // The two row halves are added through LDS, each wavefront ending with one
+  // tensor of its 32 keys: w takes dK, handing its dV to w + 4, and the other
+  // way round (the query-block buffers and the K/V tile are free now; four
+  // registers, 16 bytes, per lane and access).
+  constexpr int XCH = D * 32;  // floats of one wavefront's tensor
+  __bf16* const qx = kq == 0 ? q_buf0 : kq == 1 ? q_buf1 : kq == 2 ? o_buf0 : o_buf1;
+  static_assert(XCH * 4 <= KV_BQ * D * 2 && 4 * XCH * 4 <= 2 * KV_BN * D * 2, "exchange fits the buffers");
+  f32x4* const to_hi = reinterpret_cast<f32x4*>(qx) + lane;                              // dV of w for w + 4
+  f32x4* const to_lo = reinterpret_cast<f32x4*>(kv_tile) + kq * (XCH / 4) + lane;  // dK of w + 4 for w
+  auto quad = [](const f32x16& v, int g4) { return f32x4{v[4 * g4], v[4 * g4 + 1], v[4 * g4 + 2], v[4 * g4 + 3]}; };
+  f32x16 r[D / 32];
+  if (qs == 0) {
 #pragma unroll
-  for (int round = 0; round < 2; ++round) {
-    f32x16* acc = round == 0 ? dk : dv;
-    if (qs == 1) {
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db)
+      for (int g4 = 0; g4 < 4; ++g4) to_hi[(db * 4 + g4) * 64] = quad(dv[db], g4);
+  } else {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) myx[(db * 16 + i) * 64 + lane] = acc[db][i];
-    }
-    __syncthreads();
-    if (qs == 0) {
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[db][i] += myx[(db * 16 + i) * 64 + lane];
-    }
-    __syncthreads();
+      for (int g4 = 0; g4 < 4; ++g4) to_lo[(db * 4 + g4) * 64] = quad(dk[db], g4);
   }
-  if (qs != 0) return;
+  __syncthreads();
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const f32x4 x = (qs == 0 ? to_lo : to_hi)[(db * 4 + g4) * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[db][4 * g4 + e] = (qs == 0 ? dk[db][4 * g4 + e] : dv[db][4 * g4 + e]) + x[e];
+    }
 
+  // r: dK (qs = 0) or dV (qs = 1); lane holds column d = 32*db + l32, rows = keys acc_row(i, hf)
   if (nparts > 1) {  // partial sums, in the accumulators' order (see dkv_combine_kernel)
     float* const dst = p.part + ((int64_t)(kv_item_slot(it.code) + part) * p.hkv + kvh) * (2 * KV_BN * D);
 #pragma unroll
-    for (int ts = 0; ts < 2; ++ts)
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const f32x16& a = ts == 0 ? dk[db] : dv[db];
-          *reinterpret_cast<float4*>(dst + 4 * ((((ts * 4 + kq) * (D / 32) + db) * 4 + g4) * 64 + lane)) =
-              make_float4(a[g4 * 4 + 0], a[g4 * 4 + 1], a[g4 * 4 + 2], a[g4 * 4 + 3]);
-        }
+      for (int g4 = 0; g4 < 4; ++g4)
+        *reinterpret_cast<f32x4*>(dst + 4 * ((((qs * 4 + kq) * (D / 32) + db) * 4 + g4) * 64 + lane)) = quad(r[db], g4);
     return;
   }
-
-  // dK/dV tile: lane holds column d = 32*db + l32, rows = keys acc_row(i, hf)
-  uint16_t* const dk16 = (t.flags & KV_OUT_BF16) ? p.dk[pk] : nullptr;
-  uint16_t* const dv16 = (t.flags & KV_OUT_BF16) ? p.dv[pk] : nullptr;
-  const int64_t slab = p.slab_rows * kvstride;
-  float* const dk32 = (t.flags & KV_OUT_SLAB) ? p.slab + (int64_t)t.out_row0 * kvstride : nullptr;
+  const int nkeys = min(32, t.kv_len - kw0);
+  if (nkeys <= 0) return;
+  if (qs == 0) {
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db) {
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int key = kw0 + acc_row(i, hf);
-      if (key < t.kv_len) {
-        const int64_t col = kvh * D + db * 32 + l32;
-        const int64_t off = ((int64_t)t.kv_row0 + key) * kvstride + col;
-        const float kval = dk[db][i] * p.scale, vval = dv[db][i];
-        if (dk32) {
-          const int64_t so = (int64_t)key * kvstride + col;
-          dk32[so] = kval;
-          dk32[slab + so] = vval;
-        }
-        if (dk16) {
-          reinterpret_cast<__bf16*>(dk16)[off] = (__bf16)kval;
-          reinterpret_cast<__bf16*>(dv16)[off] = (__bf16)vval;
-        }
-      }
-    }
+      for (int i = 0; i < 16; ++i) r[db][i] *= p.scale;
+  }
+  // Whole rows through the region this wavefront has just read (a store
+  // straight from r writes 2 bytes per lane and 64 bytes per row).
+  char* const buf = reinterpret_cast<char*>(qs == 0 ? to_lo - lane : to_hi - lane);
+  if (t.flags & KV_OUT_SLAB) {
+    float* const lds = reinterpret_cast<float*>(buf);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) lds[acc_row(i, hf) * D + db * 32 + l32] = r[db][i];
+    float* const dst = p.slab + (qs * p.slab_rows + t.out_row0 + kw0) * kvstride + kvh * D;
+    store_rows<D>(lds, dst, kvstride, nkeys, lane);
+  }
+  if (t.flags & KV_OUT_BF16) {
+    __bf16* const lds = reinterpret_cast<__bf16*>(buf);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) lds[acc_row(i, hf) * D + db * 32 + l32] = (__bf16)r[db][i];
+    uint16_t* const o16 = qs == 0 ? p.dk[pk] : p.dv[pk];
+    store_rows<D>(lds, reinterpret_cast<__bf16*>(o16) + (t.kv_row0 + kw0) * kvstride + kvh * D, kvstride, nkeys, lane);
   }
 }
 
@@ -705,6 +721,8 @@ hipError_t launch_attn_dq(const DqParams& p0, int n_tiles, hipStream_t stream) {
   if (n_tiles == 0) return hipSuccess;
   DqParams p = p0;
   p.n_units = n_tiles * p.hkv;
+  p.hkv_magic = div_magic(p.hkv);
+  p.group_magic = div_magic(p.group);
   const dim3 grid((unsigned)xcd_grid(p.n_units, p.group)), block(256);
   if (p.head_dim == 128) hipLaunchKernelGGL((attn_dq_kernel<128>), grid, block, 0, stream, p);
   else hipLaunchKernelGGL((attn_dq_kernel<64>), grid, block, 0, stream, p);

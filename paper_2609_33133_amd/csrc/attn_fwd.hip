@@ -45,13 +45,13 @@ template <int D, bool OUT32>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   __shared__ __bf16 k_buf0[BN * D], k_buf1[BN * D], v_buf0[BN * D], v_buf1[BN * D];
   int unit, hh;
-  if (!xcd_unit(p.n_units, p.group, unit, hh)) return;
+  if (!xcd_unit(p.n_units, p.group, p.group_magic, unit, hh)) return;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches below
-  const int tile_id = unit / p.hkv;
+  const int tile_id = fast_div(unit, p.hkv, p.hkv_magic);
   const int kvh = unit - tile_id * p.hkv;
   const QTile t = load_tile(p.tiles, p.inl, tile_id);
-  const QRows rows(t, p.group, hh, wave, l32);
+  const QRows rows(t, p.group, p.group_magic, hh, wave, l32);
   if (!rows.any) return;
   // prompt rows (prefill) or response rows (replay): tensors of the tile
   const bool prow = (t.flags & QT_PROMPT_ROWS) != 0;
@@ -65,24 +65,6 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   // head kvh, plus a 32-bit offset
   const int64_t qbase = t.q_row0 * qstride + (int64_t)kvh * p.group * D;
   const int qoff = qi * (int)qstride + rows.head * D;
-
-  // Q^T operand (B of S^T = K Q^T): lane holds query qi, d = 16*ks + 8*hf .. +7
-  bf16x8 qreg[D / 16];
-  {
-    const uint16_t* qp = qsrc + qbase + qoff + hf * 8;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks)
-      qreg[ks] = as_bf16x8(ldg16(qp + ks * 16));
-  }
-
-  const float c = p.scale_log2;
-  float m_run = -INFINITY;  // running max of raw q.k over this lane's query
-  float l_run = 0.f;        // this half-wave's share of the running sum
-  f32x16 oacc[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
 
   const int nA = (t.a_len + BN - 1) / BN;
   // segment B up to the workgroup's last row
@@ -122,6 +104,32 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   };
   auto load_k = [&](__bf16* dst) { load_next(kcur, kb0p, dst); };
   auto load_v = [&](__bf16* dst) { load_next(vcur, vb0p, dst); };
+
+  // the first blocks' copies go out before anything else is computed: K(b + 1)
+  // and V(b) are resident while block b is processed
+  if (nblk > 0) {
+    load_k(k_buf0);
+    load_v(v_buf0);
+    if (nblk > 1) load_k(k_buf1);
+  }
+
+  // Q^T operand (B of S^T = K Q^T): lane holds query qi, d = 16*ks + 8*hf .. +7
+  bf16x8 qreg[D / 16];
+  {
+    const uint16_t* qp = qsrc + qbase + qoff + hf * 8;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks)
+      qreg[ks] = as_bf16x8(ldg16(qp + ks * 16));
+  }
+
+  const float c = p.scale_log2;
+  float m_run = -INFINITY;  // running max of raw q.k over this lane's query
+  float l_run = 0.f;        // this half-wave's share of the running sum
+  f32x16 oacc[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
 
   RowOffsets<D> k_off;  // K row l32; row 32 + l32 has the same swizzle, 32 rows further
   k_off.init(l32, hf);
@@ -238,14 +246,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
     set_wave_priority<0>();
   };
 
-  // K(b + 1) and V(b) are resident while block b is processed; iteration b
-  // loads K(b + 2) over K(b) and V(b + 1) over V(b - 1).
+  // iteration b loads K(b + 2) over K(b) and V(b + 1) over V(b - 1)
   f32x16 sa0, sa1, sb0, sb1;
-  if (nblk > 0) {
-    load_k(k_buf0);
-    load_v(v_buf0);
-    if (nblk > 1) load_k(k_buf1);
-  }
   wait_vmem();
   __syncthreads();
   s_mfma(k_buf0, sa0, sa1);
@@ -267,44 +269,31 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   }
 
   const float l_tot = pair_sum(l_run);
+  const bool part1 = (t.flags & QT_PART1) != 0;
   // (the lane's row again, instead of registers held over the sweep)
-  const QRows er(t, p.group, hh, wave, (int)opaque(l32));
-  if (er.valid) {
-    const int eoff = er.row * (int)qstride + er.head * D;
-    const float inv = 1.f / l_tot;
-    const bool part1 = (t.flags & QT_PART1) != 0;
-    float* const o32 = p.o32 + (part1 ? p.o32_part : 0) + qbase;
-    uint16_t* const o16 = (prow ? p.o[1] : p.o[0]) + qbase;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int d0 = db * 32 + g4 * 8 + hf * 4;
-        const float v0 = oacc[db][g4 * 4 + 0] * inv, v1 = oacc[db][g4 * 4 + 1] * inv;
-        const float v2 = oacc[db][g4 * 4 + 2] * inv, v3 = oacc[db][g4 * 4 + 3] * inv;
-        if constexpr (OUT32) {
-          *reinterpret_cast<float4*>(o32 + eoff + d0) = make_float4(v0, v1, v2, v3);
-        } else {
-          typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-          bf16x4 w;
-          w[0] = (__bf16)v0; w[1] = (__bf16)v1; w[2] = (__bf16)v2; w[3] = (__bf16)v3;
-          *reinterpret_cast<bf16x4*>(o16 + eoff + d0) = w;
-        }
-      }
+  const QRows er(t, p.group, p.group_magic, hh, wave, (int)opaque(l32));
+  if (er.valid && hf == 0) {
+    float* lse;
+    int64_t lrows;
+    if constexpr (OUT32) {
+      lse = p.lse[0] + (part1 ? p.lse_part : 0);
+      lrows = p.lse_rows[0];
+    } else {
+      lse = prow ? p.lse[1] : p.lse[0];
+      lrows = prow ? p.lse_rows[1] : p.lse_rows[0];
     }
-    if (hf == 0) {
-      float* lse;
-      int64_t lrows;
-      if constexpr (OUT32) {
-        lse = p.lse[0] + (part1 ? p.lse_part : 0);
-        lrows = p.lse_rows[0];
-      } else {
-        lse = prow ? p.lse[1] : p.lse[0];
-        lrows = prow ? p.lse_rows[1] : p.lse_rows[0];
-      }
-      lse[(int64_t)(kvh * p.group + er.head) * lrows + t.q_row0 + er.row] = (m_run * c + __log2f(l_tot)) * kLn2;
-    }
+    lse[(int64_t)(kvh * p.group + er.head) * lrows + t.q_row0 + er.row] = (m_run * c + __log2f(l_tot)) * kLn2;
   }
+  if (!rows.wave_any) return;
+  // through this wavefront's own buffer (nothing is in flight any more)
+  char* const buf = reinterpret_cast<char*>(wave == 0 ? k_buf0 : wave == 1 ? k_buf1 : wave == 2 ? v_buf0 : v_buf1);
+  const float inv = 1.f / l_tot;
+  if constexpr (OUT32)
+    store_pairs<D>(buf, oacc, inv, p.o32 + (part1 ? p.o32_part : 0) + qbase, qstride, t, p.group, p.group_magic, hh,
+                   wave, lane);
+  else
+    store_pairs<D>(buf, oacc, inv, reinterpret_cast<__bf16*>(prow ? p.o[1] : p.o[0]) + qbase, qstride, t, p.group, p.group_magic, hh, wave,
+                   lane);
 }
 
 }  // namespace
@@ -313,6 +302,8 @@ hipError_t launch_attn_fwd(const FwdParams& p0, int n_tiles, bool out_f32, hipSt
   if (n_tiles == 0) return hipSuccess;
   FwdParams p = p0;
   p.n_units = n_tiles * p.hkv;
+  p.hkv_magic = div_magic(p.hkv);
+  p.group_magic = div_magic(p.group);
   const dim3 grid((unsigned)xcd_grid(p.n_units, p.group)), block(256);
   if (p.head_dim == 128) {
     if (out_f32) hipLaunchKernelGGL((attn_fwd_kernel<128, true>), grid, block, 0, stream, p);

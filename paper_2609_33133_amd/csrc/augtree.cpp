@@ -382,23 +382,26 @@ std::atomic<int> g_tree_chunk_blocks{kTreeChunkBlocksDefault};
 // prompt with many response rows, few KV heads) leaves most of the chip idle
 // behind its prompt tiles. Such a tile's sweep is cut into parts, which a
 // second kernel adds in part order. The rule reads the tile's own tree alone,
-// so that a tree's results do not depend on the batch: with `load` the tree's
-// block steps over the chip's 256 workgroup slots, its tiles are cut into
-// parts of max(load, kSplitMinBlocks) blocks if its longest sweep is at least
-// kSplitRatio times that. Measured (dK/dV launch and the addition): three
-// trees of P = 384 .. 1337 with 8 query and 2 KV heads, load 7 .. 25 blocks,
-// sweeps up to 352: 473 us unsplit, 131 us with parts of 32, 163 with 64, 146
-// with 16; one tree of P = 1500 with 16 / 4 heads (d = 64), load 105: 454
-// against 171 us. A part costs about 12 us of one workgroup slot (its
-// prologue and its 128 KB of partial sums written and read again), which is
-// lost where the batch's other trees fill the chip: four trees of P = 233 ..
-// 1811 with 32 / 8 heads, 463 us unsplit and 492 split, though their sweeps
-// are 2.3 .. 5.4 times their own loads. kSplitRatio leaves the nearly balanced
-// trees alone: a causal sequence of 4096 with 8 KV heads (1.94 times the
-// load) together with one of 1025 takes 337 us split and 395 unsplit, six of
-// 333 .. 4096 together 658 split and 630 unsplit.
-constexpr int kSplitMinBlocks = 32;
-constexpr double kSplitRatio = 1.75;
+// so that a tree's results do not depend on the batch. Let `load` be the
+// tree's block steps over the chip's 256 workgroup slots. A part costs about
+// 12 us (6 blocks) of one slot, its prologue and its 128 KB of partial sums
+// written and read again, which is lost where the batch's other trees fill
+// the chip. So a tree is split where its longest sweep is kSplitRatio times
+// both the load and kSplitBlocks, into parts as long as the larger of the two
+// (at most about 10 % lost); where the sweep is kSplitFineRatio times the
+// load, kSplitFineBlocks takes the place of kSplitBlocks. Measured (dK/dV launch and the
+// addition): three trees of P = 384 .. 1337 with 8 query and 2 KV heads, load
+// 7 .. 25 blocks, sweeps up to 352: 473 us unsplit, 146 with parts of 16, 131
+// with 32, 163 with 64, 276 with 128; one tree of P = 1500 with 16 / 4 heads
+// (d = 64), load 105, sweeps of 476: 454 against 171 us. Nearly balanced
+// trees in a batch lose: four with 32 / 8 heads and sweeps of 2.3 .. 5.4
+// times the load, 463 us unsplit and 492 with parts of 32; 32 causal
+// sequences of 1024, 64 blocks at most, the whole backward 1190 us unsplit
+// and 1386 with parts of 32.
+constexpr int kSplitBlocks = 64;
+constexpr int kSplitRatio = 3;
+constexpr int kSplitFineBlocks = 32;
+constexpr int kSplitFineRatio = 8;
 
 int64_t q_blocks(int64_t rows) { return cdiv(rows, kDkvBlockQ); }
 
@@ -412,8 +415,12 @@ int64_t split_blocks(const Shape& s, int g, int bn) {
     for (int b = s.cb[g]; b < s.cb[g + 1]; ++b)
       for (int k0 = 0, R = s.cr[b + 1] - s.cr[b]; k0 < R; k0 += bn) all += q_blocks(R - k0);
   const int64_t longest = (q_blocks(nr) + q_blocks(P)) * s.group;
-  const int64_t per = std::max<int64_t>(kSplitMinBlocks, all * s.group * s.hkv / 256);
-  if ((double)longest < kSplitRatio * (double)per) return 0;
+  const int64_t load = all * s.group * s.hkv / 256;
+  int64_t per = std::max<int64_t>(kSplitBlocks, load);
+  if (longest >= kSplitFineRatio * load && longest >= kSplitRatio * kSplitFineBlocks)
+    per = std::max<int64_t>(kSplitFineBlocks, load);
+  else if (longest < kSplitRatio * per)
+    return 0;
   return std::max<int64_t>(per, cdiv(longest, kMaxParts));
 }
 
@@ -809,6 +816,7 @@ int run_bwd(const Shape& s, const Plan& pl, const Tensors& x, const BwdOut& out,
     p.lse_rows[0] = s.tr; p.lse_rows[1] = s.tp;
     p.dk[0] = out.dk_r; p.dv[0] = out.dv_r; p.dk[1] = out.dk_p; p.dv[1] = out.dv_p;
     p.slab = out.slab; p.slab_rows = out.slab_rows;
+    p.hkv_magic = div_magic(s.hkv);
     p.hq = s.hq; p.hkv = s.hkv; p.group = s.group; p.head_dim = s.d; p.scale = s.scale; p.scale_log2 = sl2;
     HookScope h(role_dkv, str);
     if ((st = hip_status(launch_attn_dkv(p, (int)pl.kv.v.size(), str), "dkv launch"))) return st;

@@ -37,6 +37,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+// sixteen bytes of any type
+typedef uint32_t raw16 __attribute__((ext_vector_type(4), may_alias));
 
 __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -314,6 +316,12 @@ __device__ __forceinline__ T load_tile(const T* tiles, const T* inl, int i) {
   return r;
 }
 
+// n / d for 0 <= n < 2^31 with magic = div_magic(d)
+__device__ __forceinline__ int fast_div(int n, int d, uint32_t magic) {
+  const int q = magic ? (int)__umulhi((uint32_t)n, magic) : n;
+  return (uint32_t)q * (uint32_t)d > (uint32_t)n ? q - 1 : q;
+}
+
 // ---------------------------------------------------------------------------- rows of a query tile
 
 // The query kernels' 128 columns (one per lane of the four wavefronts' column
@@ -337,19 +345,66 @@ struct QRows {
   bool valid;         // this lane's pair exists
   int row, head;      // this lane's row of the tile and query head of the group
 
-  __device__ __forceinline__ QRows(const QTile& t, int g, int sub, int wave, int l32) {
+  __device__ __forceinline__ QRows(const QTile& t, int g, uint32_t magic, int sub, int wave, int l32) {
     const int n = t.q_len * g, c0 = sub * 128, w0 = c0 + wave * 32;
     any = c0 < n;
     wave_any = w0 < n;
-    wlo = w0 / g;
-    whi = min(w0 + 31, n - 1) / g;
-    last = min(c0 + 127, n - 1) / g;
+    wlo = fast_div(w0, g, magic);
+    whi = fast_div(min(w0 + 31, n - 1), g, magic);
+    last = fast_div(min(c0 + 127, n - 1), g, magic);
     valid = w0 + l32 < n;
     const int c = valid ? w0 + l32 : n - 1;  // lanes without a pair repeat the last one and write nothing
-    row = c / g;
+    row = fast_div(c, g, magic);
     head = c - row * g;
   }
 };
+
+// Writes the [32 pairs, D] result tile of a wavefront (lane: pair l32, columns
+// 32 db + acc_row(i, hf) in acc[db][i]) to out, the tile's first row at KV head
+// kvh, as T. Straight from the accumulators a store instruction would touch
+// 32 rows with 16 bytes each; through `buf` (32 D sizeof(T) bytes of LDS of
+// this wavefront alone, chunks of 16 bytes XOR-swizzled by row) each one
+// writes whole rows, and the g heads of a row are contiguous in memory.
+// (With the direct stores a workgroup of the forward spent 5900 of the 30,000
+// cycles it took for a 512-token sequence here.)
+template <int D, class T>
+__device__ __forceinline__ void store_pairs(char* buf, const f32x16* acc, float mul, T* out, int64_t qstride,
+                                            const QTile& t, int g, uint32_t magic, int sub, int wave, int lane) {
+  constexpr int CPR = D * sizeof(T) / 16;  // 16-byte chunks of a row
+  constexpr int RPI = 64 / CPR;            // rows of one store instruction
+  const int l32 = lane & 31, hf = lane >> 5;
+  char* const row = buf + l32 * (CPR * 16);
+  const int sw = l32 & (CPR - 1);
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db) {
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const f32x4 v = {acc[db][g4 * 4] * mul, acc[db][g4 * 4 + 1] * mul, acc[db][g4 * 4 + 2] * mul,
+                       acc[db][g4 * 4 + 3] * mul};
+      const int col = db * 32 + g4 * 8 + hf * 4;
+      if constexpr (sizeof(T) == 4) {
+        *reinterpret_cast<f32x4*>(row + (((col >> 2) ^ sw) << 4)) = v;
+      } else {
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        bf16x4 w;
+        w[0] = (__bf16)v[0]; w[1] = (__bf16)v[1]; w[2] = (__bf16)v[2]; w[3] = (__bf16)v[3];
+        *reinterpret_cast<bf16x4*>(row + (((col >> 3) ^ sw) << 4) + (col & 4) * 2) = w;
+      }
+    }
+  }
+  const int n = t.q_len * g, w0 = sub * 128 + wave * 32;
+  const int ch = lane & (CPR - 1), r0 = lane / CPR;
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int r = r0 + i * RPI;
+    const raw16 v = *reinterpret_cast<const raw16*>(buf + r * (CPR * 16) + ((ch ^ (r & (CPR - 1))) << 4));
+    if (w0 + r < n) {
+      const int q = fast_div(w0 + r, g, magic);
+      char* const dst = reinterpret_cast<char*>(out + q * qstride + (w0 + r - q * g) * D);
+      *reinterpret_cast<raw16*>(dst + ch * 16) = v;
+    }
+  }
+}
 
 // ---------------------------------------------------------------------------- workgroup order
 
@@ -357,11 +412,12 @@ struct QRows {
 // its own L2. Units of `per_unit` consecutive workgroups (the query heads of
 // one KV head on one tile) are kept on one XCD, and units are dealt to XCDs
 // in schedule order (heaviest first). Returns false for padding workgroups.
-__device__ __forceinline__ bool xcd_unit(int n_units, int per_unit, int& unit, int& sub) {
+__device__ __forceinline__ bool xcd_unit(int n_units, int per_unit, uint32_t magic, int& unit, int& sub) {
   const int i = blockIdx.x;
   const int x = i & 7, j = i >> 3;
-  unit = (j / per_unit) * 8 + x;
-  sub = j % per_unit;
+  const int q = fast_div(j, per_unit, magic);
+  unit = q * 8 + x;
+  sub = j - q * per_unit;
   return unit < n_units;
 }
 

@@ -15,6 +15,12 @@ namespace augtree {
 
 constexpr int kInlineTiles = 32;
 
+// Division by a launch constant d on the device: q = mulhi(n, magic), one too
+// large at most (fast_div in common.h corrects it). magic = ceil(2^32 / d),
+// and 0 for d = 1. (A 32-bit division costs a scalar wavefront about 40
+// dependent instructions; a workgroup needs five before its first load.)
+inline uint32_t div_magic(int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+
 struct FwdParams {
   const QTile* tiles;         // device schedule, or nullptr: `inl`
   const uint16_t* q[2];       // [rows, hq, d]
@@ -30,7 +36,8 @@ struct FwdParams {
   int64_t lse_part;
   int hq, hkv, group, head_dim;
   float scale_log2;           // softmax_scale * log2(e)
-  int n_units;                // tiles x KV heads (set by the launcher)
+  int n_units;                // tiles x KV heads (set by the launcher, as the magic numbers)
+  uint32_t hkv_magic, group_magic;
   QTile inl[kInlineTiles];
 };
 
@@ -51,6 +58,7 @@ struct DqParams {
   int hq, hkv, group, head_dim;
   float scale, scale_log2;
   int n_units;
+  uint32_t hkv_magic, group_magic;
   QTile inl[kInlineTiles];
 };
 
@@ -69,6 +77,7 @@ struct DkvParams {
   int64_t slab_rows;
   int hq, hkv, group, head_dim;
   float scale, scale_log2;
+  uint32_t hkv_magic;
   // split sweeps (n_items > 0): the launch's workgroups, the tiles whose
   // parts have to be added (code: first slot, part 0, nparts) and the fp32
   // scratch of the partial sums, [slots][hkv][2][128 x d]

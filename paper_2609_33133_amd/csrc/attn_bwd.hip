@@ -318,8 +318,7 @@ __device__ __forceinline__ KVItem load_item(const DkvParams& p, int i) {
     if (p.items) {
       r = p.items[i];
     } else {
-      const uint32_t w = p.inl_items[i];
-      r = KVItem{(int32_t)(w >> 27), w & 0x7ffffffu};
+      r = p.inline_item(i);
     }
   }
   r.tile = __builtin_amdgcn_readfirstlane(r.tile);
@@ -682,8 +681,7 @@ __global__ __launch_bounds__(COMBINE_THREADS) void dkv_combine_kernel(DkvParams 
   if (p.combine) {
     it = p.combine[e];
   } else {
-    const uint32_t w = p.inl_combine[e];
-    it = KVItem{(int32_t)(w >> 27), w & 0x7ffffffu};
+    it = p.inline_combine(e);
   }
   it.tile = __builtin_amdgcn_readfirstlane(it.tile);
   it.code = __builtin_amdgcn_readfirstlane(it.code);

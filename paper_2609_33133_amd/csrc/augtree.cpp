@@ -544,12 +544,17 @@ struct Plan {
     bytes = std::max<size_t>(o, kAlign);
   }
   static bool inline_list(size_t n) { return n <= (size_t)kInlineTiles; }
+  // the key tiles with their items (one word each), which share the space
+  bool inline_kv() const {
+    const size_t n = kv.v.size();
+    return inline_list(n) && items.size() + combine.size() <= (kInlineTiles - n) * (sizeof(KVTile) / sizeof(uint32_t));
+  }
   // bytes of the workspace prefix that must be uploaded (0: every list inline)
   size_t upload_bytes() const {
     size_t end = 0;
     for (int i = 0; i < 3; ++i)
       if (!inline_list(q[i].v.size())) end = off_q[i] + q[i].v.size() * sizeof(QTile);
-    if (!inline_list(kv.v.size())) {
+    if (!inline_kv()) {
       end = off_kv + kv.v.size() * sizeof(KVTile);
       if (!combine.empty()) end = off_combine + combine.size() * sizeof(KVItem);
     }
@@ -561,7 +566,7 @@ struct Plan {
     for (int i = 0; i < 3; ++i)
       if (!inline_list(q[i].v.size()))
         std::memcpy(blob.data() + off_q[i], q[i].v.data(), q[i].v.size() * sizeof(QTile));
-    if (!inline_list(kv.v.size())) {
+    if (!inline_kv()) {
       std::memcpy(blob.data() + off_kv, kv.v.data(), kv.v.size() * sizeof(KVTile));
       if (!combine.empty()) {
         std::memcpy(blob.data() + off_items, items.data(), items.size() * sizeof(KVItem));
@@ -575,8 +580,8 @@ struct Plan {
 // Points the launch parameters at list i: the workspace copy, or the kernel
 // arguments' inline copy.
 template <class P, class T>
-void bind_tiles(P& p, const TileList<T>& L, void* ws, size_t off) {
-  if (Plan::inline_list(L.v.size())) {
+void bind_tiles(P& p, const TileList<T>& L, bool is_inline, void* ws, size_t off) {
+  if (is_inline) {
     p.tiles = nullptr;
     std::copy(L.v.begin(), L.v.end(), p.inl);
   } else {
@@ -591,10 +596,11 @@ void bind_split(DkvParams& p, const Plan& pl, void* ws) {
   p.n_items = (int)pl.items.size();
   p.n_combine = (int)pl.combine.size();
   p.part = reinterpret_cast<float*>(base + pl.off_part);
-  if (Plan::inline_list(pl.kv.v.size())) {
-    auto word = [](const KVItem& it) { return (uint32_t)it.tile << 27 | it.code; };
-    std::transform(pl.items.begin(), pl.items.end(), p.inl_items, word);
-    std::transform(pl.combine.begin(), pl.combine.end(), p.inl_combine, word);
+  if (pl.inline_kv()) {
+    auto word = [](const KVItem& it) { return (uint32_t)it.tile << 24 | it.code; };
+    uint32_t* const w = reinterpret_cast<uint32_t*>(p.inl + p.n_inline);
+    std::transform(pl.items.begin(), pl.items.end(), w, word);
+    std::transform(pl.combine.begin(), pl.combine.end(), w + pl.items.size(), word);
   } else {
     p.items = reinterpret_cast<const KVItem*>(base + pl.off_items);
     p.combine = reinterpret_cast<const KVItem*>(base + pl.off_combine);
@@ -743,13 +749,13 @@ int run_fwd(const Shape& s, const Plan& pl, int mode, const Tensors& x, uint16_t
   p.hq = s.hq; p.hkv = s.hkv; p.group = s.group; p.head_dim = s.d;
   p.scale_log2 = log2e_scale(s.scale);
   if (!pl.q[0].v.empty()) {
-    bind_tiles(p, pl.q[0], ws, pl.off_q[0]);
+    bind_tiles(p, pl.q[0], Plan::inline_list(pl.q[0].v.size()), ws, pl.off_q[0]);
     HookScope h(role_main, str);
     if ((st = hip_status(launch_attn_fwd(p, (int)pl.q[0].v.size(), false, str), "forward launch"))) return st;
   }
   if (pl.q[1].v.empty()) return AUGTREE_OK;
   // split groups: both partial states in one launch, then the merge
-  bind_tiles(p, pl.q[1], ws, pl.off_q[1]);
+  bind_tiles(p, pl.q[1], Plan::inline_list(pl.q[1].v.size()), ws, pl.off_q[1]);
   p.o32 = o_part; p.o32_part = s.tr * s.hq * s.d;
   p.lse[0] = lse_part; p.lse_part = s.tr * s.hq;
   {
@@ -789,7 +795,7 @@ int run_bwd(const Shape& s, const Plan& pl, const Tensors& x, const BwdOut& out,
   const float sl2 = log2e_scale(s.scale);
   if (!pl.q[0].v.empty()) {
     DqParams p{};
-    bind_tiles(p, pl.q[0], ws, pl.off_q[0]);
+    bind_tiles(p, pl.q[0], Plan::inline_list(pl.q[0].v.size()), ws, pl.off_q[0]);
     p.q[0] = x.q_r; p.q[1] = x.q_p;
     p.dout[0] = x.do_r; p.dout[1] = x.do_p;
     p.o[0] = x.o_r; p.o[1] = x.o_p;
@@ -806,7 +812,8 @@ int run_bwd(const Shape& s, const Plan& pl, const Tensors& x, const BwdOut& out,
   }
   if (!pl.kv.v.empty()) {
     DkvParams p{};
-    bind_tiles(p, pl.kv, ws, pl.off_kv);
+    bind_tiles(p, pl.kv, pl.inline_kv(), ws, pl.off_kv);
+    p.n_inline = p.tiles ? 0 : (int)pl.kv.v.size();
     bind_split(p, pl, ws);
     p.k[0] = x.k_r; p.v[0] = x.v_r; p.k[1] = x.k_p; p.v[1] = x.v_p;
     p.q[0] = x.q_r; p.q[1] = x.q_p;

@@ -13,7 +13,11 @@
 
 namespace augtree {
 
-constexpr int kInlineTiles = 32;
+// (Kernel arguments are limited to 4 KB.) An uploaded schedule costs a copy
+// of 5 us on the stream before the launch: the forward of 99 tiles (8 query
+// heads) 75 us with it and 69 without; the longer arguments cost nothing
+// measurable.
+constexpr int kInlineTiles = 112;
 
 // Division by a launch constant d on the device: q = mulhi(n, magic), one too
 // large at most (fast_div in common.h corrects it). magic = ceil(2^32 / d),
@@ -81,14 +85,21 @@ struct DkvParams {
   // split sweeps (n_items > 0): the launch's workgroups, the tiles whose
   // parts have to be added (code: first slot, part 0, nparts) and the fp32
   // scratch of the partial sums, [slots][hkv][2][128 x d]
-  const KVItem* items;        // device, or nullptr: `inl_items`
-  const KVItem* combine;      // device, or nullptr: `inl_combine`
+  const KVItem* items;        // device, or nullptr: words after the inline tiles
+  const KVItem* combine;      // device, or nullptr: words after those
   int n_items, n_combine;
+  int n_inline;               // tiles in `inl`
   float* part;
-  KVTile inl[kInlineTiles];
-  uint32_t inl_items[kInlineTiles * kMaxParts];
-  uint32_t inl_combine[kInlineTiles];
+  KVTile inl[kInlineTiles];   // n_inline tiles, then n_items and n_combine item words
+
+  // item (combine: tile to add) i of the kernel arguments
+  __host__ __device__ KVItem inline_item(int i) const {
+    const uint32_t w = reinterpret_cast<const uint32_t*>(inl + n_inline)[i];
+    return KVItem{(int32_t)(w >> 24), w & 0xffffffu};
+  }
+  __host__ __device__ KVItem inline_combine(int i) const { return inline_item(n_items + i); }
 };
+static_assert(sizeof(FwdParams) <= 4096 && sizeof(DqParams) <= 4096 && sizeof(DkvParams) <= 4096, "kernel arguments");
 
 // fp32 values of one scratch slot and KV head (dK and dV of a 128-key tile)
 inline int64_t dkv_part_elems(int head_dim) { return 2 * (int64_t)kDkvBlockN * head_dim; }

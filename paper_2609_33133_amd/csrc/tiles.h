@@ -76,9 +76,9 @@ enum : int32_t {
 // same query rows). A tile with nparts = 1 writes its outputs; the parts of a
 // split tile write fp32 partial sums to the consecutive scratch slots
 // slot0 + part, which a combine kernel adds in part order. code = slot0 << 8 |
-// part << 4 | (nparts - 1). A launch whose tiles travel in the kernel
-// arguments (at most 32) carries its items there as one word each: tile <<
-// 27 | code (slot0 < 512).
+// part << 4 | (nparts - 1). A launch whose tiles and items fit the
+// kernel arguments carries its items there as one word each: tile << 24 |
+// code (tile < 256, slot0 < 65536).
 struct KVItem {
   int32_t tile;
   uint32_t code;

@@ -63,17 +63,14 @@ hipError_t launch_attn_dkv(const DkvParams& p, int n, hipStream_t) {
   ++g_split;
   g_inline += !p.items;
   CHECK((p.items == nullptr) == (p.tiles == nullptr));
-  CHECK(p.items || p.n_items <= kInlineTiles * kMaxParts);
-  auto item = [&](const KVItem* dev, const uint32_t* inl, int i) {
-    return dev ? dev[i] : KVItem{(int32_t)(inl[i] >> 27), inl[i] & 0x7ffffffu};
-  };
+  CHECK(p.items || (p.n_inline == n && 4 * (p.n_items + p.n_combine) <= (int)sizeof(KVTile) * (kInlineTiles - n)));
   const size_t slot_bytes = (size_t)p.hkv * 2 * kDkvBlockN * p.head_dim * sizeof(float);
   CHECK((const char*)p.part >= g_ws && ((uintptr_t)p.part & 15) == 0);
   std::vector<std::vector<char>> seen(n);
   std::vector<char> slots;
   std::vector<uint32_t> first(n, ~0u);
   for (int i = 0; i < p.n_items; ++i) {
-    const KVItem it = item(p.items, p.inl_items, i);
+    const KVItem it = p.items ? p.items[i] : p.inline_item(i);
     CHECK(it.tile >= 0 && it.tile < n);
     const int np = kv_item_nparts(it.code), part = kv_item_part(it.code);
     CHECK(part < np && np <= kMaxParts);
@@ -100,7 +97,7 @@ hipError_t launch_attn_dkv(const DkvParams& p, int n, hipStream_t) {
   }
   std::vector<char> added(n, 0);
   for (int i = 0; i < p.n_combine; ++i) {
-    const KVItem it = item(p.combine, p.inl_combine, i);
+    const KVItem it = p.combine ? p.combine[i] : p.inline_combine(i);
     CHECK(it.tile >= 0 && it.tile < n && !added[it.tile]);
     added[it.tile] = 1;
     CHECK(kv_item_nparts(it.code) == g_parts[it.tile] && (uint32_t)kv_item_slot(it.code) == first[it.tile]);

@@ -49,7 +49,8 @@
  *   D = rowsum(dO * O) of every row there (written by its dQ kernel, read by
  *   its dK/dV kernel), and the fp32 partial sums of key tiles whose sweep is
  *   split (trees with few key tiles and long sweeps; a second kernel of the
- *   dK/dV launch adds them).
+ *   dK/dV launch adds them). A backward whose workspace has no room for those
+ *   runs these sweeps whole: the same gradients up to fp32 summation order.
  * Errors: every call returns an augtree_status. Arguments are validated on
  *   the host before any work is enqueued; on error nothing is launched and
  *   augtree_last_error() gives a detail string (thread-local). No C++

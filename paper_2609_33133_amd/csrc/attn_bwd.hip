@@ -3,7 +3,8 @@
 // D = rowsum(dO * O), dP = dO V^T, dS = P (dP - D):
 //   dQ = s dS K,   dK = s dS^T Q,   dV = P^T dO.
 //
-// Two kernels, no atomics, every output written once:
+// Two kernels (and the addition of split sweeps, dkv_combine_kernel), no
+// atomics, every output written once:
 // * attn_dq_kernel (query-outer): one workgroup (4 wavefronts, two workgroups
 //   per CU) per 128 (query row, head) pairs of one KV head (QRows), sweeping the same key
 //   segments as the forward (prompt keys, then the branch's own causal keys)
@@ -14,10 +15,11 @@
 //   per 128-key tile and KV head. Wavefronts w and w + 4 own the same 32 keys
 //   (K and V tiles in LDS) and take the two 32-row halves of
 //   every 64-row query block; their dK/dV partials are added through LDS at
-//   the end. The sweep covers every query that sees the keys: the g query
+//   the end, one tensor by each of the two. The sweep covers every query that sees the keys: the g query
 //   heads of the KV head (GQA) and, for prompt keys in replay, the response
 //   rows of every branch of the group, so the Eq. 2 sum over branches happens
-//   in the accumulators. Query tiles are copied to LDS directly from global
+//   in the accumulators (long sweeps of trees with few key tiles are cut into
+//   parts, KVItem). Query tiles are copied to LDS directly from global
 //   memory; Q^T and dO^T operands come from transpose reads.
 #include "common.h"
 #include "kernels.h"

@@ -608,7 +608,9 @@ void bind_split(DkvParams& p, const Plan& pl, void* ws) {
 }
 
 // Operation codes of augtree_workspace_size beyond the public four.
-Plan plan_for(const Shape& s, int op, int arg) {
+// `split`: long dK/dV sweeps in parts (a backward without the room for their
+// partial sums runs them whole).
+Plan plan_for(const Shape& s, int op, int arg, bool split = true) {
   Plan pl;
   const int bm = fwd_block_m(), bn = dkv_block_n(), bq = dkv_block_q();
   switch (op) {
@@ -648,8 +650,7 @@ Plan plan_for(const Shape& s, int op, int arg) {
       break;
     case AUGTREE_OP_TREE_BWD: {
       // arg bit 0: the fp32 copy of the prompt-key gradient is requested too;
-      // bit 1: no chunked prompt-key sweeps, bit 2: no split sweeps (both keep
-      // the workspace small)
+      // bit 1: no chunked prompt-key sweeps (keeps the workspace small)
       add_prefill_qtiles(pl.q[0], s, dq_block_m());
       add_replay_qtiles(pl.q[0], s, dq_block_m(), RP_FUSED);
       add_response_kvtiles(pl.kv, s, bn);
@@ -672,7 +673,7 @@ Plan plan_for(const Shape& s, int op, int arg) {
         // a workspace slab; the reduce adds the chunks in order
         std::vector<int64_t> vbase(s.ng + 1, 0);
         for (int g = 0; g < s.ng; ++g) vbase[g + 1] = vbase[g] + (int64_t)nc[g] * (s.cp[g + 1] - s.cp[g]);
-        if (vbase[s.ng] > INT32_MAX) return plan_for(s, op, arg | 2);  // slab rows are int32
+        if (vbase[s.ng] > INT32_MAX) return plan_for(s, op, arg | 2, split);  // slab rows are int32
         for (int g = 0; g < s.ng; ++g) {
           const int64_t P = s.cp[g + 1] - s.cp[g], nr = s.cr[s.cb[g + 1]] - s.cr[s.cb[g]];
           for (int c = 0; c < nc[g]; ++c) {
@@ -696,8 +697,17 @@ Plan plan_for(const Shape& s, int op, int arg) {
       break;
   }
   pl.sort(s);
-  if (!(op == AUGTREE_OP_TREE_BWD && (arg & 4))) pl.split(s, bn);
+  if (split) pl.split(s, bn);
   pl.layout(s.hq, (int64_t)s.hkv * s.d);
+  return pl;
+}
+
+// A backward plan for a workspace of ws_bytes: with split sweeps if there is
+// room for their partial sums, else without (a workspace that was sized for
+// another batch keeps working; the same sums in another fp32 order).
+Plan plan_for_ws(const Shape& s, int op, int arg, size_t ws_bytes) {
+  Plan pl = plan_for(s, op, arg);
+  if (pl.slots > 0 && pl.bytes > ws_bytes) pl = plan_for(s, op, arg, false);
   return pl;
 }
 
@@ -1000,7 +1010,7 @@ int augtree_replay_bwd(const augtree_groups* grp, const uint16_t* q_r, const uin
   REQUIRE_PTR(q_r); REQUIRE_PTR(k_r); REQUIRE_PTR(v_r); REQUIRE_PTR(k_p); REQUIRE_PTR(v_p);
   REQUIRE_PTR(o_r); REQUIRE_PTR(lse_r); REQUIRE_PTR(do_r);
   REQUIRE_PTR(dq_r); REQUIRE_PTR(dk_r); REQUIRE_PTR(dv_r); REQUIRE_PTR(dkv_p_seed);
-  Plan pl = plan_for(s, AUGTREE_OP_REPLAY_BWD, n_seed);
+  Plan pl = plan_for_ws(s, AUGTREE_OP_REPLAY_BWD, n_seed, ws_bytes);
   if ((st = check_ws(pl, ws, ws_bytes))) return st;
   if ((st = check_device_impl())) return st;
   hipStream_t str = static_cast<hipStream_t>(stream);
@@ -1025,7 +1035,7 @@ int augtree_prefill_bwd(const augtree_groups* grp, const uint16_t* q_p, const ui
   OPTIONAL_PTR(dq_p); OPTIONAL_PTR(dq_p_f32);
   if (!dq_p && !dq_p_f32) return fail(AUGTREE_ERR_INVALID_ARGUMENT, "no dQ output (dq_p and dq_p_f32 both null)");
   REQUIRE_PTR(dkv_p_self);
-  Plan pl = plan_for(s, AUGTREE_OP_PREFILL_BWD, 0);
+  Plan pl = plan_for_ws(s, AUGTREE_OP_PREFILL_BWD, 0, ws_bytes);
   if ((st = check_ws(pl, ws, ws_bytes))) return st;
   if ((st = check_device_impl())) return st;
   hipStream_t str = static_cast<hipStream_t>(stream);
@@ -1064,14 +1074,12 @@ int tree_bwd_impl(const augtree_groups* grp, const uint16_t* q_p, const uint16_t
   REQUIRE_PTR(q_r); REQUIRE_PTR(k_r); REQUIRE_PTR(v_r); REQUIRE_PTR(o_r); REQUIRE_PTR(lse_r); REQUIRE_PTR(do_r);
   REQUIRE_PTR(dq_p); REQUIRE_PTR(dk_p); REQUIRE_PTR(dv_p); REQUIRE_PTR(dq_r); REQUIRE_PTR(dk_r); REQUIRE_PTR(dv_r);
   OPTIONAL_PTR(dkv_p_f32);
-  Plan pl = plan_for(s, AUGTREE_OP_TREE_BWD, dkv_p_f32 ? 1 : 0);
+  const int arg = dkv_p_f32 ? 1 : 0;
+  Plan pl = plan_for_ws(s, AUGTREE_OP_TREE_BWD, arg, ws_bytes);
   if (scratch) {  // the caller's buffer is a fixed device array: check its size before touching the device
-    // split and chunked sweeps need fp32 partial sums; without room for them,
-    // first no splits, then one sweep per key tile (the same sums in another
-    // fp32 order)
-    const int arg = dkv_p_f32 ? 1 : 0;
-    if (pl.bytes > ws_bytes && pl.slots > 0) pl = plan_for(s, AUGTREE_OP_TREE_BWD, arg | 4);
-    if (pl.bytes > ws_bytes && pl.n_parts > 0) pl = plan_for(s, AUGTREE_OP_TREE_BWD, arg | 6);
+    // chunked prompt-key sweeps need an fp32 slab; without room for it, one
+    // sweep per prompt key tile (the same sum in another fp32 order)
+    if (pl.bytes > ws_bytes && pl.n_parts > 0) pl = plan_for(s, AUGTREE_OP_TREE_BWD, arg | 2, false);
     if (pl.bytes > ws_bytes)
       return fail(AUGTREE_ERR_WORKSPACE,
                   "this batch needs %zu bytes of scratch; the allocation-free entry point holds at most %zu bytes",

@@ -17,7 +17,8 @@
 using namespace augtree;
 
 namespace {
-int g_fail = 0, g_split = 0, g_inline = 0, g_max_parts = 0;
+int g_fail = 0, g_split = 0, g_inline = 0, g_max_parts = 0, g_fallback = 0;
+bool g_launch_split = false;
 const char* g_ws = nullptr;
 size_t g_ws_bytes = 0;
 std::vector<int> g_parts;  // parts per tile of the last dK/dV launch, keyed by schedule order
@@ -61,6 +62,7 @@ hipError_t launch_attn_dkv(const DkvParams& p, int n, hipStream_t) {
     return hipSuccess;
   }
   ++g_split;
+  g_launch_split = true;
   g_inline += !p.items;
   CHECK((p.items == nullptr) == (p.tiles == nullptr));
   CHECK(p.items || (p.n_inline == n && 4 * (p.n_items + p.n_combine) <= (int)sizeof(KVTile) * (kInlineTiles - n)));
@@ -135,6 +137,20 @@ void run(const std::vector<int>& ps, const std::vector<std::vector<int>>& rs, in
     else
       st = augtree_prefill_bwd(&g, u(1), u(2), u(3), u(4), f(5), u(13), u(14), nullptr, f(15), ws, g_ws_bytes, nullptr);
     CHECK(st == AUGTREE_OK);
+    if (which < 2 && g_launch_split) {
+      // a workspace without room for the partial sums: accepted, whole sweeps
+      const size_t full = g_ws_bytes;
+      for (size_t less = 256; less < full; less *= 2) {
+        g_ws_bytes = full - less;
+        g_launch_split = false;
+        st = augtree_tree_bwd(&g, u(1), u(2), u(3), u(4), f(5), u(13), u(6), u(7), u(8), u(9), f(10), u(16), u(14),
+                              u(21), u(22), which ? f(23) : nullptr, u(17), u(18), u(19), ws, g_ws_bytes, nullptr);
+        if (st == AUGTREE_OK) ++g_fallback;
+        else CHECK(st == AUGTREE_ERR_WORKSPACE);
+        if (less > 4096) CHECK(!g_launch_split);
+      }
+    }
+    g_launch_split = false;
     std::free(ws);
   }
 }
@@ -164,8 +180,8 @@ int main() {
     const int hk = rnd(1, 3);
     run(ps, rs, hk * rnd(1, 8), hk, rnd(0, 1) ? 128 : 64);
   }
-  if (g_fail || !g_inline || g_max_parts < 8) {
-    std::printf("%d failures (%d inline, most parts %d)\n", g_fail, g_inline, g_max_parts);
+  if (g_fail || !g_inline || g_max_parts < 8 || g_fallback < 20) {
+    std::printf("%d failures (%d inline, most parts %d, %d fallbacks)\n", g_fail, g_inline, g_max_parts, g_fallback);
     return 1;
   }
   std::printf("ok %d\n", g_split);

@@ -273,7 +273,9 @@ int augtree_tree_fwd(const augtree_groups* grp, int mode, const uint16_t* q_p, c
  * "reduce_tree"). Long sweeps otherwise lose the L2 sharing of the query rows.
  * The prompt gradient is the same sum as the three-call path up to fp32
  * rounding order (that path adds two fp32 partial sums); it is bitwise
- * reproducible for a given chunk setting. dQ carries the same common-mode
+ * reproducible for a given chunk setting. The dK/dV launch is followed by a
+ * small one that adds the parts of split sweeps, where the batch has any (both
+ * under the role "dkv_tree"). dQ carries the same common-mode
  * correction as augtree_replay_bwd.
  * In:  q_p, k_p, v_p, o_p (bf16), lse_p (fp32), do_p (bf16) [prompt rows];
  *      q_r, k_r, v_r, o_r (bf16), lse_r (fp32), do_r (bf16) [response rows].

@@ -396,7 +396,7 @@ std::atomic<int> g_tree_chunk_blocks{kTreeChunkBlocksDefault};
 // (d = 64), load 105, sweeps of 476: 454 against 171 us. Nearly balanced
 // trees in a batch lose: four with 32 / 8 heads and sweeps of 2.3 .. 5.4
 // times the load, 463 us unsplit and 492 with parts of 32; 32 causal
-// sequences of 1024, 64 blocks at most, the whole backward 1190 us unsplit
+// sequences of 1024, 64 blocks at most, the whole backward 1262 us unsplit
 // and 1386 with parts of 32.
 constexpr int kSplitBlocks = 64;
 constexpr int kSplitRatio = 3;

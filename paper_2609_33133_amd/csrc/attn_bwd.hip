@@ -299,18 +299,21 @@ constexpr int KV_BQ = kDkvBlockQ;  // query rows per block (32 per wavefront of 
 constexpr int DKV_SDP_DEPTH = 3;  // LDS operand reads of S / dP run this many MFMAs ahead
 constexpr int DKV_DVK_DEPTH = 2;  // the same for the dV / dK transpose reads
 
-// Copies up to 32 rows of D elements from LDS (dense) to rows of `dst`, 16
-// bytes per lane.
+// Copies up to 32 rows of D elements, written by this wavefront, from LDS
+// (dense) to rows of `dst`, 16 bytes per lane; `lds` may be written again
+// afterwards.
 template <int D, class T>
 __device__ __forceinline__ void store_rows(const T* lds, T* dst, int64_t stride, int nrows, int lane) {
   constexpr int CPR = D * sizeof(T) / 16, RPI = 64 / CPR;
   const int ch = lane & (CPR - 1), r0 = lane / CPR;
+  wave_lds_fence();
 #pragma unroll
   for (int i = 0; i < 32 / RPI; ++i) {
     const int r = r0 + i * RPI;
     const raw16 v = reinterpret_cast<const raw16*>(lds + r * D)[ch];
     if (r < nrows) reinterpret_cast<raw16*>(dst + r * stride)[ch] = v;
   }
+  wave_lds_fence();
 }
 
 // Workgroup unit `i` of a launch: its item, or the whole tile i.
@@ -643,6 +646,7 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   }
   // Whole rows through the region this wavefront has just read (a store
   // straight from r writes 2 bytes per lane and 64 bytes per row).
+  wave_lds_fence();
   char* const buf = reinterpret_cast<char*>(qs == 0 ? to_lo - lane : to_hi - lane);
   if (t.flags & KV_OUT_SLAB) {
     float* const lds = reinterpret_cast<float*>(buf);

@@ -322,6 +322,17 @@ __device__ __forceinline__ int fast_div(int n, int d, uint32_t magic) {
   return (uint32_t)q * (uint32_t)d > (uint32_t)n ? q - 1 : q;
 }
 
+// Orders the LDS accesses of this wavefront's lanes: what any lane wrote
+// before it is what any lane reads after it, and what a lane read before it may
+// be overwritten after it. LDS accesses of one wavefront complete in issue
+// order, so this costs no instruction; it keeps the compiler, which sees one
+// lane at a time, from moving an access across.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------- rows of a query tile
 
 // The query kernels' 128 columns (one per lane of the four wavefronts' column
@@ -392,6 +403,7 @@ __device__ __forceinline__ void store_pairs(char* buf, const f32x16* acc, float 
       }
     }
   }
+  wave_lds_fence();
   const int n = t.q_len * g, w0 = sub * 128 + wave * 32;
   const int ch = lane & (CPR - 1), r0 = lane / CPR;
 #pragma unroll
@@ -404,6 +416,7 @@ __device__ __forceinline__ void store_pairs(char* buf, const f32x16* acc, float 
       *reinterpret_cast<raw16*>(dst + ch * 16) = v;
     }
   }
+  wave_lds_fence();  // buf may be written again
 }
 
 // ---------------------------------------------------------------------------- workgroup order

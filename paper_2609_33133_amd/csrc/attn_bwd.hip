@@ -53,10 +53,10 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   const int qi = rows.row;
   const int64_t qstride = (int64_t)p.hq * D;
   const int64_t kvstride = (int64_t)p.hkv * D;
-  // this lane's elements in Q / dO / O / dQ (uniform start, 32-bit offset) and
+  // this lane's elements in Q / dO / O (uniform start, the pair's offset) and
   // its LSE and D
   const int64_t qbase = t.q_row0 * qstride + (int64_t)kvh * p.group * D;
-  const int qoff = qi * (int)qstride + rows.head * D;
+  const int64_t qoff = pair_offset<D>(qi, rows.head, p.hq);
   const int64_t srow = (int64_t)(kvh * p.group + rows.head) * lrows + t.q_row0 + qi;
 
   const int nA = (t.a_len + DQ_BN - 1) / DQ_BN;
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(DqParams p) {
   bf16x8 qreg[D / 16], doreg[D / 16];
   float dsq;
   {
-    const int off = qoff + hf * 8;
+    const int64_t off = qoff + hf * 8;
     const uint16_t* qs = (prow ? p.q[1] : p.q[0]) + qbase + off;
     const uint16_t* ds = (prow ? p.dout[1] : p.dout[0]) + qbase + off;
     const uint16_t* os = (prow ? p.o[1] : p.o[0]) + qbase + off;

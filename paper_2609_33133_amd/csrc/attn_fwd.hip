@@ -61,10 +61,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   const int qi = rows.row;
   const int64_t qstride = (int64_t)p.hq * D;
   const int64_t kvstride = (int64_t)p.hkv * D;
-  // this lane's elements in Q / O: uniform start of the tile's rows of KV
-  // head kvh, plus a 32-bit offset
+  // this lane's elements in Q: uniform start of the tile's rows of KV head
+  // kvh, plus the pair's offset
   const int64_t qbase = t.q_row0 * qstride + (int64_t)kvh * p.group * D;
-  const int qoff = qi * (int)qstride + rows.head * D;
+  const int64_t qoff = pair_offset<D>(qi, rows.head, p.hq);
 
   const int nA = (t.a_len + BN - 1) / BN;
   // segment B up to the workgroup's last row

@@ -32,6 +32,14 @@ struct QTile {
   int32_t flags;  // QT_*
 };
 
+// Element offset of (row, head) of a query tile from its first row at its KV
+// head, in a [*, hq, D] tensor. 64 bits: 128 rows of 132,105 heads of 128 pass
+// 2^31 elements.
+template <int D>
+__host__ __device__ inline int64_t pair_offset(int row, int head, int hq) {
+  return (int64_t)row * hq * D + head * D;
+}
+
 enum : int32_t {
   // the query rows are prompt rows (Q_P, O_P, LSE_P; segment B = prompt
   // keys); otherwise response rows (Q_R, O_R, LSE_R; segment B = the

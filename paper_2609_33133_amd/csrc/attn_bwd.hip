@@ -30,7 +30,6 @@ namespace {
 
 // ----------------------------------------------------------------------------- dQ
 
-constexpr int DQ_BM = kDqBlockM;
 constexpr int DQ_BN = kDqBlockN;
 constexpr int DQ_DEPTH = 4;  // LDS operand reads run this many MFMAs ahead
 

@@ -30,7 +30,6 @@ namespace augtree {
 
 namespace {
 
-constexpr int BM = kFwdBlockM;  // query rows per workgroup
 constexpr int BN = kFwdBlockN;  // keys per block
 constexpr int FWD_DEPTH = 4;  // LDS operand reads run this many MFMAs ahead
 constexpr int PV_DEPTH = 3;   // the same for the P V MFMAs (two reads each)

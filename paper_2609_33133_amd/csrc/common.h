@@ -338,7 +338,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // The query kernels' 128 columns (one per lane of the four wavefronts' column
 // index) are the (row, head) pairs of a tile, row-major over the g query
 // heads of one KV head: workgroup `sub` of a tile takes pairs 128 sub ..
-// 128 sub + 127, i.e. about 128 / g rows of all g heads, which share the K/V
+// 128 sub + 127 (kPairsPerWorkgroup), i.e. about 128 / g rows of all g heads, which share the K/V
 // blocks as well as 128 rows of one head do. A tile of few rows (a short
 // branch, the ragged end of a segment) fills ceil(q_len g / 128) workgroups
 // instead of g mostly empty ones, and a workgroup's causal range ends at its
@@ -357,12 +357,12 @@ struct QRows {
   int row, head;      // this lane's row of the tile and query head of the group
 
   __device__ __forceinline__ QRows(const QTile& t, int g, uint32_t magic, int sub, int wave, int l32) {
-    const int n = t.q_len * g, c0 = sub * 128, w0 = c0 + wave * 32;
+    const int n = t.q_len * g, c0 = sub * kPairsPerWorkgroup, w0 = c0 + wave * 32;
     any = c0 < n;
     wave_any = w0 < n;
     wlo = fast_div(w0, g, magic);
     whi = fast_div(min(w0 + 31, n - 1), g, magic);
-    last = fast_div(min(c0 + 127, n - 1), g, magic);
+    last = fast_div(min(c0 + kPairsPerWorkgroup - 1, n - 1), g, magic);
     valid = w0 + l32 < n;
     const int c = valid ? w0 + l32 : n - 1;  // lanes without a pair repeat the last one and write nothing
     row = fast_div(c, g, magic);
@@ -404,7 +404,7 @@ __device__ __forceinline__ void store_pairs(char* buf, const f32x16* acc, float 
     }
   }
   wave_lds_fence();
-  const int n = t.q_len * g, w0 = sub * 128 + wave * 32;
+  const int n = t.q_len * g, w0 = sub * kPairsPerWorkgroup + wave * 32;
   const int ch = lane & (CPR - 1), r0 = lane / CPR;
 #pragma unroll
   for (int i = 0; i < 32 / RPI; ++i) {

@@ -21,6 +21,12 @@ constexpr int kDqBlockN = 64;     // dQ: keys per block
 constexpr int kDkvBlockN = 128;   // dK/dV: keys per tile
 constexpr int kDkvBlockQ = 64;    // dK/dV: query rows per block
 
+// (row, head) pairs of a forward or dQ workgroup, 32 per wavefront. A tile is
+// launched as g workgroups per KV head (g query heads each), which hold all
+// its pairs only while it has at most this many rows.
+constexpr int kPairsPerWorkgroup = 128;
+static_assert(kFwdBlockM <= kPairsPerWorkgroup && kDqBlockM <= kPairsPerWorkgroup, "a tile's pairs fit its workgroups");
+
 // Query tile of the forward and dQ kernels: up to BM query rows, attending to
 // segment A (prompt keys, every key visible) and then segment B (causal:
 // query i of the tile sits at segment position b_qpos + i and sees keys

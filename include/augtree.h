@@ -47,10 +47,15 @@
  *   on `stream` (the host staging happens before the call returns); smaller
  *   schedules travel in the kernel arguments. The backward also keeps
  *   D = rowsum(dO * O) of every row there (written by its dQ kernel, read by
- *   its dK/dV kernel), and the fp32 partial sums of key tiles whose sweep is
- *   split (trees with few key tiles and long sweeps; a second kernel of the
- *   dK/dV launch adds them). A backward whose workspace has no room for those
- *   runs these sweeps whole: the same gradients up to fp32 summation order.
+ *   its dK/dV kernel), and the fp32 sums of key tiles whose sweep is split
+ *   into parts (trees with few key tiles and long sweeps): of each part where
+ *   the parts are workgroups of their own (a second kernel of the dK/dV launch
+ *   adds them), or of the tile where one workgroup runs them one after the
+ *   other (batches that fill the GPU). A tile or part takes
+ *   2 x 128 x Hkv x d x 4 bytes. Both ways give the same bits. A backward whose
+ *   workspace has no room for the parts runs them in one workgroup; without
+ *   room for that either it runs these sweeps whole: the same gradients up to
+ *   fp32 summation order.
  * Errors: every call returns an augtree_status. Arguments are validated on
  *   the host before any work is enqueued; on error nothing is launched and
  *   augtree_last_error() gives a detail string (thread-local). No C++
@@ -298,12 +303,10 @@ int augtree_tree_bwd(const augtree_groups* grp, const uint16_t* q_p, const uint1
  * augtree_tree_bwd without a workspace argument, for callers that cannot
  * allocate device memory (code under stream capture, tight serving loops,
  * harnesses that forbid allocation). Same inputs, outputs and results as
- * augtree_tree_bwd (bit for bit: same kernels and schedule, except that a
- * batch whose split or chunked schedule does not fit the array runs without
- * the splits, and if need be with one sweep per prompt-key tile: the same
- * gradients up to fp32 summation order). Its
- * workspace is
- * a fixed 64 MiB device array of the library (augtree_noalloc_scratch_bytes()),
+ * augtree_tree_bwd (bit for bit, except that a batch whose split sweeps do not
+ * fit the array even with one slot a tile runs them whole, and one whose
+ * chunks do not fit runs one sweep per prompt-key tile: the same gradients up
+ * to fp32 summation order). Its workspace is a fixed 64 MiB device array of the library (augtree_noalloc_scratch_bytes()),
  * one copy per GPU, held from the first call on that GPU until the process
  * ends; the call performs no allocation. A batch whose unchunked workspace
  * exceeds it is rejected with AUGTREE_ERR_WORKSPACE before anything is

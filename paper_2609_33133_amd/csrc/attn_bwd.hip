@@ -330,7 +330,16 @@ __device__ __forceinline__ KVItem load_item(const DkvParams& p, int i) {
   return r;
 }
 
-template <int D>
+// SERIAL: the launch has tiles whose parts run one after the other
+// (KV_SERIAL). A kernel of its own: the other launches keep the shorter
+// exchange and code (both sweep at the same speed: 64 trees of 4400 tokens,
+// whole sweeps, 3268 and 3272 us for the backward). A change of part takes
+// 4.1 us, about two blocks and a half: four barriers around the exchange,
+// 128 KB of running sums read and written, the next part's first block loaded
+// with nothing to overlap it. (Requesting that block before the running sum
+// gained nothing; with the LDS addresses recomputed in the block loop, see
+// below, the whole sweep was 16 % slower.)
+template <int D, bool SERIAL>
 __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   // the workgroup's K and V tiles (operands of S = Q K^T and dP = dO V^T);
   // query blocks double-buffered in separate arrays, with -LSE / scale and
@@ -382,10 +391,11 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   const int nxblk = p.group * nxb;
   const int nall = nxblk + p.group * nyb;
   // this workgroup's share of them, in sweep order
-  const int part = kv_item_part(it.code);
+  int part = kv_item_part(it.code);
   const int part_len = t.flags >> KV_PART_SHIFT;
   const int blk0 = part * part_len;
-  const int nblk = part + 1 < nparts ? part_len : nall - blk0;
+  int nblk = part + 1 < nparts ? part_len : nall - blk0;
+  const bool serial = SERIAL && (t.flags & KV_SERIAL) != 0;
 
   // Query blocks in sweep order: (range, query head of the group, 64-row
   // block). Inside a range the blocks are swept from the end backwards and
@@ -539,6 +549,12 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
       for (int e = 0; e < 4; ++e) { s[g4 * 4 + e] = l4[e]; dp[g4 * 4 + e] = d4[e]; }
     }
     set_wave_priority<0>();
+    // (inside two loops the compiler would take the address apart again and
+    // add the tile's base before every read: 16 % on the whole sweep)
+    if constexpr (SERIAL) {
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+v"(key_off.o[ks]));
+    }
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
       s = mfma32(lds_row8_at<D>(ql, qrow_off.o[ks]), lds_read16(kv_tile, key_off.o[ks]), s);
@@ -572,67 +588,110 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   };
 
   Blk c0{0, 0}, c1{0, 0};
-  if (nblk > 0) {
-    load_next(q_buf0, o_buf0, c0);
-    store_stat(nlse_buf0, ndsum_buf0);
-  }
-  wait_vmem();
-  __syncthreads();
-  for (int b = 0; b < nblk; b += 2) {
-    if (b + 1 < nblk) load_next(q_buf1, o_buf1, c1);
-    compute(c0, q_buf0, o_buf0, nlse_buf0, ndsum_buf0);
-    if (b + 1 < nblk) store_stat(nlse_buf1, ndsum_buf1);
-    wait_vmem();
-    __syncthreads();
-    if (b + 1 < nblk) {
-      if (b + 2 < nblk) load_next(q_buf0, o_buf0, c0);
-      compute(c1, q_buf1, o_buf1, nlse_buf1, ndsum_buf1);
-      if (b + 2 < nblk) store_stat(nlse_buf0, ndsum_buf0);
-      wait_vmem();
-      __syncthreads();
-    }
-  }
-
-  // The two row halves are added through LDS, each wavefront ending with one
-  // tensor of its 32 keys: w takes dK, handing its dV to w + 4, and the other
-  // way round (the query-block buffers and the K/V tile are free now; four
-  // registers, 16 bytes, per lane and access).
+  // After the sweep the two row halves are added through LDS, each wavefront
+  // ending with one tensor of its 32 keys: w takes dK, handing its dV to
+  // w + 4, and the other way round (the query-block buffers and the K/V tile
+  // are free then; four registers, 16 bytes, per lane and access).
   constexpr int XCH = D * 32;  // floats of one wavefront's tensor
   __bf16* const qx = kq == 0 ? q_buf0 : kq == 1 ? q_buf1 : kq == 2 ? o_buf0 : o_buf1;
   static_assert(XCH * 4 <= KV_BQ * D * 2 && 4 * XCH * 4 <= 2 * KV_BN * D * 2, "exchange fits the buffers");
-  f32x4* const to_hi = reinterpret_cast<f32x4*>(qx) + lane;                              // dV of w for w + 4
-  f32x4* const to_lo = reinterpret_cast<f32x4*>(kv_tile) + kq * (XCH / 4) + lane;  // dK of w + 4 for w
+  f32x4* const to_hi = reinterpret_cast<f32x4*>(qx);                        // dV of w for w + 4
+  f32x4* const to_lo = reinterpret_cast<f32x4*>(kv_tile) + kq * (XCH / 4);  // dK of w + 4 for w
   auto quad = [](const f32x16& v, int g4) { return f32x4{v[4 * g4], v[4 * g4 + 1], v[4 * g4 + 2], v[4 * g4 + 3]}; };
-  f32x16 r[D / 32];
-  if (qs == 0) {
+  auto put = [&](f32x4* dst, const f32x16* v, int lane) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) to_hi[(db * 4 + g4) * 64] = quad(dv[db], g4);
-  } else {
+      for (int g4 = 0; g4 < 4; ++g4) dst[(db * 4 + g4) * 64 + lane] = quad(v[db], g4);
+  };
+  auto add = [&](f32x16* v, const f32x4* src, int lane) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) to_lo[(db * 4 + g4) * 64] = quad(dk[db], g4);
-  }
-  __syncthreads();
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 x = src[(db * 4 + g4) * 64 + lane];
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      const f32x4 x = (qs == 0 ? to_lo : to_hi)[(db * 4 + g4) * 64];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) r[db][4 * g4 + e] = (qs == 0 ? dk[db][4 * g4 + e] : dv[db][4 * g4 + e]) + x[e];
+        for (int e = 0; e < 4; ++e) v[db][4 * g4 + e] += x[e];
+        // (all loads at once do not fit the registers beside dK and dV)
+        if (SERIAL && D == 128 && db == 1 && g4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+  };
+  // this wavefront's share of a scratch slot, in the accumulators' order (see
+  // dkv_combine_kernel)
+  auto slot_quads = [&](int slot) {
+    return reinterpret_cast<f32x4*>(p.part + ((int64_t)slot * p.hkv + kvh) * (2 * KV_BN * D) + (qs * 4 + kq) * XCH);
+  };
+
+  for (;;) {
+    if (nblk > 0) {
+      load_next(q_buf0, o_buf0, c0);
+      store_stat(nlse_buf0, ndsum_buf0);
+    }
+    wait_vmem();
+    __syncthreads();
+    for (int b = 0; b < nblk; b += 2) {
+      if (b + 1 < nblk) load_next(q_buf1, o_buf1, c1);
+      compute(c0, q_buf0, o_buf0, nlse_buf0, ndsum_buf0);
+      if (b + 1 < nblk) store_stat(nlse_buf1, ndsum_buf1);
+      wait_vmem();
+      __syncthreads();
+      if (b + 1 < nblk) {
+        if (b + 2 < nblk) load_next(q_buf0, o_buf0, c0);
+        compute(c1, q_buf1, o_buf1, nlse_buf1, ndsum_buf1);
+        if (b + 2 < nblk) store_stat(nlse_buf0, ndsum_buf0);
+        wait_vmem();
+        __syncthreads();
+      }
     }
 
+    if constexpr (!SERIAL) {
+      if (qs == 0) put(to_hi, dv, lane);
+      else put(to_lo, dk, lane);
+      __syncthreads();
+      if (qs == 0) add(dk, to_lo, lane);
+      else add(dv, to_hi, lane);
+      break;
+    } else {
+      // (a lane index made here for the running sum's addresses: they
+      // would otherwise be computed before the sweep and spilled over it)
+      int el = lane;
+      asm volatile("" : "+v"(el));
+      // the K/V tile is needed again: both ways through the query-block
+      // buffers, one after the other
+      if (qs == 0) put(to_hi, dv, lane);
+      __syncthreads();
+      if (qs == 1) add(dv, to_hi, lane);
+      __syncthreads();
+      if (qs == 1) put(to_hi, dk, lane);
+      __syncthreads();
+      if (qs == 0) add(dk, to_hi, lane);
+      __syncthreads();
+      if (!serial) break;
+      f32x4* const sum = slot_quads(kv_item_slot(it.code));
+      if (part > 0) {
+        if (qs == 0) add(dk, sum, el);
+        else add(dv, sum, el);
+      }
+      if (++part == nparts) break;
+      if (qs == 0) put(sum, dk, el);
+      else put(sum, dv, el);
+      nblk = part + 1 < nparts ? part_len : nall - part * part_len;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { dk[db][i] = 0.f; dv[db][i] = 0.f; }
+    }
+  }
+  f32x16 r[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db) {
+    r[db] = dv[db];
+    if (qs == 0) r[db] = dk[db];
+  }
+
   // r: dK (qs = 0) or dV (qs = 1); lane holds column d = 32*db + l32, rows = keys acc_row(i, hf)
-  if (nparts > 1) {  // partial sums, in the accumulators' order (see dkv_combine_kernel)
-    float* const dst = p.part + ((int64_t)(kv_item_slot(it.code) + part) * p.hkv + kvh) * (2 * KV_BN * D);
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4)
-        *reinterpret_cast<f32x4*>(dst + 4 * ((((qs * 4 + kq) * (D / 32) + db) * 4 + g4) * 64 + lane)) = quad(r[db], g4);
+  if (nparts > 1 && !serial) {  // partial sums
+    put(slot_quads(kv_item_slot(it.code) + part), r, lane);
     return;
   }
   const int nkeys = min(32, t.kv_len - kw0);
@@ -646,7 +705,7 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
   // Whole rows through the region this wavefront has just read (a store
   // straight from r writes 2 bytes per lane and 64 bytes per row).
   wave_lds_fence();
-  char* const buf = reinterpret_cast<char*>(qs == 0 ? to_lo - lane : to_hi - lane);
+  char* const buf = reinterpret_cast<char*>(qs == 0 ? to_lo : to_hi);
   if (t.flags & KV_OUT_SLAB) {
     float* const lds = reinterpret_cast<float*>(buf);
 #pragma unroll
@@ -735,8 +794,13 @@ hipError_t launch_attn_dq(const DqParams& p0, int n_tiles, hipStream_t stream) {
 hipError_t launch_attn_dkv(const DkvParams& p, int n_tiles, hipStream_t stream) {
   if (n_tiles == 0) return hipSuccess;
   const dim3 grid((unsigned)(p.n_items > 0 ? p.n_items : n_tiles) * (unsigned)p.hkv), block(512);
-  if (p.head_dim == 128) hipLaunchKernelGGL((attn_dkv_kernel<128>), grid, block, 0, stream, p);
-  else hipLaunchKernelGGL((attn_dkv_kernel<64>), grid, block, 0, stream, p);
+  if (p.head_dim == 128) {
+    if (p.serial) hipLaunchKernelGGL((attn_dkv_kernel<128, true>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((attn_dkv_kernel<128, false>), grid, block, 0, stream, p);
+  } else {
+    if (p.serial) hipLaunchKernelGGL((attn_dkv_kernel<64, true>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((attn_dkv_kernel<64, false>), grid, block, 0, stream, p);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_combine == 0) return e;
   const unsigned per_tile = (unsigned)(dkv_part_elems(p.head_dim) / (4 * COMBINE_THREADS));

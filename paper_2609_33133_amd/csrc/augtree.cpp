@@ -380,24 +380,23 @@ std::atomic<int> g_tree_chunk_blocks{kTreeChunkBlocksDefault};
 // Split of long dK/dV sweeps. A key tile is one workgroup per KV head and
 // its sweep is serial, so a tree with few key tiles and long sweeps (a short
 // prompt with many response rows, few KV heads) leaves most of the chip idle
-// behind its prompt tiles. Such a tile's sweep is cut into parts, which a
-// second kernel adds in part order. The rule reads the tile's own tree alone,
-// so that a tree's results do not depend on the batch. Let `load` be the
-// tree's block steps over the chip's 256 workgroup slots. A part costs about
-// 12 us (6 blocks) of one slot, its prologue and its 128 KB of partial sums
-// written and read again, which is lost where the batch's other trees fill
-// the chip. So a tree is split where its longest sweep is kSplitRatio times
-// both the load and kSplitBlocks, into parts as long as the larger of the two
-// (at most about 10 % lost); where the sweep is kSplitFineRatio times the
-// load, kSplitFineBlocks takes the place of kSplitBlocks. Measured (dK/dV launch and the
-// addition): three trees of P = 384 .. 1337 with 8 query and 2 KV heads, load
-// 7 .. 25 blocks, sweeps up to 352: 473 us unsplit, 146 with parts of 16, 131
-// with 32, 163 with 64, 276 with 128; one tree of P = 1500 with 16 / 4 heads
-// (d = 64), load 105, sweeps of 476: 454 against 171 us. Nearly balanced
-// trees in a batch lose: four with 32 / 8 heads and sweeps of 2.3 .. 5.4
-// times the load, 463 us unsplit and 492 with parts of 32; 32 causal
-// sequences of 1024, 64 blocks at most, the whole backward 1262 us unsplit
-// and 1386 with parts of 32.
+// behind its prompt tiles. Such a tile's sweep is cut into parts whose sums
+// are added in part order. The cuts follow from the tile's own tree alone, so
+// that a tree's results do not depend on the batch; how the parts run
+// (split_apart) is the batch's matter. Let `load` be the tree's block steps
+// over the chip's 256 workgroup slots. A part that is a workgroup of its own
+// costs about 6 blocks of one slot, its start and end and its 128 KB of
+// partial sums, and the addition of these. So a tree is split where its
+// longest sweep is kSplitRatio times both the load and kSplitBlocks, into
+// parts as long as the larger of the two; where the sweep is kSplitFineRatio
+// times the load, kSplitFineBlocks takes the place of kSplitBlocks. Measured
+// (dK/dV launch and the addition): three trees of P = 384 .. 1337 with 8 query
+// and 2 KV heads, load 7 .. 25 blocks, sweeps up to 352: 473 us unsplit, 146
+// with parts of 16, 131 with 32, 163 with 64, 276 with 128; one tree of
+// P = 1500 with 16 / 4 heads (d = 64), load 105, sweeps of 476: 454 against
+// 171 us. kSplitRatio is a cautious choice: sweeps of up to 2.9 times the load
+// stay whole although cuts would help some of them (one causal sequence of
+// 11264, 8 / 2 heads, has 704 blocks against a load of 244).
 constexpr int kSplitBlocks = 64;
 constexpr int kSplitRatio = 3;
 constexpr int kSplitFineBlocks = 32;
@@ -423,6 +422,28 @@ int64_t split_blocks(const Shape& s, int g, int bn) {
     return 0;
   return std::max<int64_t>(per, cdiv(longest, kMaxParts));
 }
+
+// How the parts of split sweeps run: as workgroups of their own where the
+// rule below says so, else all parts of a tile in one workgroup; or no splits.
+enum SplitMode { SPLIT_AUTO, SPLIT_SERIAL, SPLIT_NONE };
+
+// Whether the parts of a tree's tiles are workgroups of their own: where the
+// tree's longest sweep (blocks) is longer than 5/4 of the launch's load, i.e.
+// of `all` block steps over the 256 workgroup slots, the launch would wait for
+// it. Elsewhere the other tiles fill the chip, and the parts run one after the
+// other in the tile's workgroup, with the same results: a part then costs 4 us
+// (the exchange of the row halves and the running sum) instead of 11 us and the
+// addition. Whole backward, no cuts / own workgroups / one workgroup, in us:
+//   n trees of P = 400 with 8 x 500, 8 / 2 heads   (280 blocks, load 13 n)
+//     n =  8    559 /  398 /  596      n = 24   1164 / 1306 / 1193
+//     n = 16    795 /  801 /  828      n = 64   3268 / 3475 / 3333
+//   n trees of P = 300 with 8 x 700, 28 / 4 heads  (651 blocks, load 61 n)
+//     n =  8   1882 / 1824 / 1945      n = 32   7179 / 7498 / 7329
+//   32 trees of P = 600 with 8 x 400, 32 / 8 heads 6384 / 6533 / 6512
+//   64 trees of P = 150 with 16 x 256, 32 / 8      7248 / 7643 / 7499
+// (The one-workgroup form keeps 2 .. 3 % of a full batch's backward for the
+// cuts that a smaller batch gains a factor of two and more from.)
+bool split_apart(int64_t longest, int64_t all, int hkv) { return longest * 256 * 4 > all * hkv * 5; }
 
 // parts of per_part blocks, the last one 0.5 .. 1.5 times as long
 int split_parts(int64_t blocks, int64_t per_part) {
@@ -462,9 +483,10 @@ struct Plan {
   std::vector<int32_t> row_map;
   size_t off_row_map = 0, off_slab = 0;
   // split sweeps of the key tiles (none: empty): the launch's workgroups, the
-  // split tiles, and the fp32 scratch of their parts
+  // tiles whose parts the combine kernel adds, and the fp32 scratch
   std::vector<KVItem> items, combine;
   int64_t slots = 0;
+  bool serial = false;  // any tile's parts run in one workgroup
   size_t off_items = 0, off_combine = 0, off_part = 0;
   std::vector<char> blob;
 
@@ -473,9 +495,9 @@ struct Plan {
     sort_segment_major(kv.v, kv.seg, kvtile_cost, conc_kvtiles(s));
   }
   // cut the sorted key tiles' long sweeps (after sort())
-  void split(const Shape& s, int bn) {
+  void split(const Shape& s, int bn, SplitMode mode) {
     const size_t n = kv.v.size();
-    if (n == 0) return;
+    if (n == 0 || mode == SPLIT_NONE) return;
     std::vector<int64_t> per(s.ng);
     bool any = false;
     for (int g = 0; g < s.ng; ++g) {
@@ -483,37 +505,48 @@ struct Plan {
       any = any || per[g] > 0;
     }
     if (!any) return;
-    std::vector<int> tree(s.nb);
+    std::vector<int> tree(s.nb), of(n), np(n, 1), slot0(n, 0);
     for (int g = 0; g < s.ng && s.nb > 0; ++g)
       for (int b = s.cb[g]; b < s.cb[g + 1]; ++b) tree[b] = g;
-    std::vector<int> np(n, 1), slot0(n, 0);
+    auto blocks = [&](size_t i) { return kvtile_cost(kv.v[i]) * s.group; };
+    std::vector<int64_t> longest(s.ng, 0);
+    int64_t all = 0;
     for (size_t i = 0; i < n; ++i) {
-      const int g = kv.seg[i] < s.ng ? kv.seg[i] : tree[kv.seg[i] - s.ng];
-      np[i] = split_parts(kvtile_cost(kv.v[i]) * s.group, per[g]);
+      of[i] = kv.seg[i] < s.ng ? kv.seg[i] : tree[kv.seg[i] - s.ng];
+      longest[of[i]] = std::max(longest[of[i]], blocks(i));
+      all += blocks(i);
+    }
+    for (size_t i = 0; i < n; ++i) {
+      const int g = of[i];
+      const bool one_wg = mode == SPLIT_SERIAL || !split_apart(longest[g], all, s.hkv);
+      np[i] = split_parts(blocks(i), per[g]);
       if (np[i] == 1) continue;
       if (slots + np[i] >= (1 << 24) || per[g] >= (1 << 23)) {  // the code's and the flags' bits
         np[i] = 1;
         continue;
       }
-      kv.v[i].flags |= (int32_t)per[g] << KV_PART_SHIFT;
+      kv.v[i].flags |= (int32_t)per[g] << KV_PART_SHIFT | (one_wg ? KV_SERIAL : 0);
       slot0[i] = (int)slots;
-      slots += np[i];
-      combine.push_back({(int32_t)i, kv_item_code(slot0[i], 0, np[i])});
+      slots += one_wg ? 1 : np[i];
+      if (one_wg) serial = true;
+      else combine.push_back({(int32_t)i, kv_item_code(slot0[i], 0, np[i])});
     }
-    if (combine.empty()) return;
+    if (slots == 0) return;
     // the parts in the order of the tiles (by segment or heaviest first);
     // equally long ones part by part, so that the workgroups that run
     // together sweep the same query rows
     std::vector<int> item_seg;
     for (int k = 0; k < kMaxParts; ++k)
       for (size_t i = 0; i < n; ++i)
-        if (k < np[i]) {
+        if (k < ((kv.v[i].flags & KV_SERIAL) ? 1 : np[i])) {
           items.push_back({(int32_t)i, kv_item_code(slot0[i], k, np[i])});
           item_seg.push_back(kv.seg[i]);
         }
     sort_segment_major(items, item_seg, [&](const KVItem& it) {
-      const int64_t all = kvtile_cost(kv.v[it.tile]) * s.group, per = kv.v[it.tile].flags >> KV_PART_SHIFT;
-      return kv_item_part(it.code) + 1 < kv_item_nparts(it.code) ? per : all - per * kv_item_part(it.code);
+      const KVTile& t = kv.v[it.tile];
+      const int64_t per = t.flags >> KV_PART_SHIFT;
+      if (t.flags & KV_SERIAL) return blocks(it.tile);
+      return kv_item_part(it.code) + 1 < kv_item_nparts(it.code) ? per : blocks(it.tile) - per * kv_item_part(it.code);
     }, conc_kvtiles(s));
   }
   // every list gets room in the workspace (its size does not depend on
@@ -556,7 +589,7 @@ struct Plan {
       if (!inline_list(q[i].v.size())) end = off_q[i] + q[i].v.size() * sizeof(QTile);
     if (!inline_kv()) {
       end = off_kv + kv.v.size() * sizeof(KVTile);
-      if (!combine.empty()) end = off_combine + combine.size() * sizeof(KVItem);
+      if (!items.empty()) end = off_combine + combine.size() * sizeof(KVItem);
     }
     if (!row_map.empty()) end = off_row_map + row_map.size() * sizeof(int32_t);
     return end;
@@ -568,10 +601,8 @@ struct Plan {
         std::memcpy(blob.data() + off_q[i], q[i].v.data(), q[i].v.size() * sizeof(QTile));
     if (!inline_kv()) {
       std::memcpy(blob.data() + off_kv, kv.v.data(), kv.v.size() * sizeof(KVTile));
-      if (!combine.empty()) {
-        std::memcpy(blob.data() + off_items, items.data(), items.size() * sizeof(KVItem));
-        std::memcpy(blob.data() + off_combine, combine.data(), combine.size() * sizeof(KVItem));
-      }
+      if (!items.empty()) std::memcpy(blob.data() + off_items, items.data(), items.size() * sizeof(KVItem));
+      if (!combine.empty()) std::memcpy(blob.data() + off_combine, combine.data(), combine.size() * sizeof(KVItem));
     }
     if (!row_map.empty()) std::memcpy(blob.data() + off_row_map, row_map.data(), row_map.size() * sizeof(int32_t));
   }
@@ -591,8 +622,9 @@ void bind_tiles(P& p, const TileList<T>& L, bool is_inline, void* ws, size_t off
 
 // The same for the items of a launch with split sweeps.
 void bind_split(DkvParams& p, const Plan& pl, void* ws) {
-  if (pl.combine.empty()) return;
+  if (pl.items.empty()) return;
   char* const base = static_cast<char*>(ws);
+  p.serial = pl.serial;
   p.n_items = (int)pl.items.size();
   p.n_combine = (int)pl.combine.size();
   p.part = reinterpret_cast<float*>(base + pl.off_part);
@@ -608,9 +640,7 @@ void bind_split(DkvParams& p, const Plan& pl, void* ws) {
 }
 
 // Operation codes of augtree_workspace_size beyond the public four.
-// `split`: long dK/dV sweeps in parts (a backward without the room for their
-// partial sums runs them whole).
-Plan plan_for(const Shape& s, int op, int arg, bool split = true) {
+Plan plan_for(const Shape& s, int op, int arg, SplitMode split_mode = SPLIT_AUTO) {
   Plan pl;
   const int bm = fwd_block_m(), bn = dkv_block_n(), bq = dkv_block_q();
   switch (op) {
@@ -673,7 +703,7 @@ Plan plan_for(const Shape& s, int op, int arg, bool split = true) {
         // a workspace slab; the reduce adds the chunks in order
         std::vector<int64_t> vbase(s.ng + 1, 0);
         for (int g = 0; g < s.ng; ++g) vbase[g + 1] = vbase[g] + (int64_t)nc[g] * (s.cp[g + 1] - s.cp[g]);
-        if (vbase[s.ng] > INT32_MAX) return plan_for(s, op, arg | 2, split);  // slab rows are int32
+        if (vbase[s.ng] > INT32_MAX) return plan_for(s, op, arg | 2, split_mode);  // slab rows are int32
         for (int g = 0; g < s.ng; ++g) {
           const int64_t P = s.cp[g + 1] - s.cp[g], nr = s.cr[s.cb[g + 1]] - s.cr[s.cb[g]];
           for (int c = 0; c < nc[g]; ++c) {
@@ -697,17 +727,20 @@ Plan plan_for(const Shape& s, int op, int arg, bool split = true) {
       break;
   }
   pl.sort(s);
-  if (split) pl.split(s, bn);
+  pl.split(s, bn, split_mode);
   pl.layout(s.hq, (int64_t)s.hkv * s.d);
   return pl;
 }
 
-// A backward plan for a workspace of ws_bytes: with split sweeps if there is
-// room for their partial sums, else without (a workspace that was sized for
-// another batch keeps working; the same sums in another fp32 order).
+// A backward plan for a workspace of ws_bytes (a workspace that was sized for
+// another batch keeps working): with the parts of split sweeps as the rule
+// has them if there is room for their sums, else each tile's parts in one
+// workgroup (the same results; one slot a tile), else whole sweeps (the same
+// sums in another fp32 order).
 Plan plan_for_ws(const Shape& s, int op, int arg, size_t ws_bytes) {
   Plan pl = plan_for(s, op, arg);
-  if (pl.slots > 0 && pl.bytes > ws_bytes) pl = plan_for(s, op, arg, false);
+  for (SplitMode m : {SPLIT_SERIAL, SPLIT_NONE})
+    if (pl.slots > 0 && pl.bytes > ws_bytes) pl = plan_for(s, op, arg, m);
   return pl;
 }
 
@@ -1079,7 +1112,7 @@ int tree_bwd_impl(const augtree_groups* grp, const uint16_t* q_p, const uint16_t
   if (scratch) {  // the caller's buffer is a fixed device array: check its size before touching the device
     // chunked prompt-key sweeps need an fp32 slab; without room for it, one
     // sweep per prompt key tile (the same sum in another fp32 order)
-    if (pl.bytes > ws_bytes && pl.n_parts > 0) pl = plan_for(s, AUGTREE_OP_TREE_BWD, arg | 2, false);
+    if (pl.bytes > ws_bytes && pl.n_parts > 0) pl = plan_for_ws(s, AUGTREE_OP_TREE_BWD, arg | 2, ws_bytes);
     if (pl.bytes > ws_bytes)
       return fail(AUGTREE_ERR_WORKSPACE,
                   "this batch needs %zu bytes of scratch; the allocation-free entry point holds at most %zu bytes",

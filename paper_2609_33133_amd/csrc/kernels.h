@@ -83,12 +83,13 @@ struct DkvParams {
   float scale, scale_log2;
   uint32_t hkv_magic;
   // split sweeps (n_items > 0): the launch's workgroups, the tiles whose
-  // parts have to be added (code: first slot, part 0, nparts) and the fp32
-  // scratch of the partial sums, [slots][hkv][2][128 x d]
+  // parts the combine kernel has to add (code: first slot, part 0, nparts) and
+  // the fp32 scratch of the partial sums, [slots][hkv][2][128 x d]
   const KVItem* items;        // device, or nullptr: words after the inline tiles
   const KVItem* combine;      // device, or nullptr: words after those
   int n_items, n_combine;
   int n_inline;               // tiles in `inl`
+  int serial;                 // any tile is KV_SERIAL
   float* part;
   KVTile inl[kInlineTiles];   // n_inline tiles, then n_items and n_combine item words
 

@@ -80,6 +80,7 @@ enum : int32_t {
   KV_X_CAUSAL = 2,
   KV_OUT_BF16 = 4,
   KV_OUT_SLAB = 8,
+  KV_SERIAL = 16,      // split tile whose parts run one after the other in one workgroup
   KV_PART_SHIFT = 8,  // flags >> KV_PART_SHIFT: blocks of a part (split tiles)
 };
 
@@ -87,9 +88,12 @@ enum : int32_t {
 // `nparts` of tile `tile`'s query blocks in sweep order. The parts are
 // flags >> KV_PART_SHIFT blocks long, the last one takes the rest (the same
 // cuts for every tile of a segment, so that parts that run together read the
-// same query rows). A tile with nparts = 1 writes its outputs; the parts of a
-// split tile write fp32 partial sums to the consecutive scratch slots
-// slot0 + part, which a combine kernel adds in part order. code = slot0 << 8 |
+// same query rows). A tile with nparts = 1 writes its outputs. The parts of a
+// split tile are added in part order, in one of two ways with the same bits:
+// each part is a workgroup that writes its fp32 sums to scratch slot
+// slot0 + part, and a combine kernel adds them; or (KV_SERIAL) one item,
+// part 0, stands for the tile, and its workgroup runs the parts one after the
+// other and keeps their running sum in slot slot0. code = slot0 << 8 |
 // part << 4 | (nparts - 1). A launch whose tiles and items fit the
 // kernel arguments carries its items there as one word each: tile << 24 |
 // code (tile < 256, slot0 < 65536).

@@ -8,6 +8,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 import torch
 
@@ -70,9 +71,10 @@ def test_split_sweeps_against_oracle(case):
 
 @pytest.mark.gpu
 def test_workspace_without_room_for_the_parts():
-    """A workspace too small for the parts' sums is accepted: the sweeps run
-    whole, the prompt gradient is the same sum in another fp32 order and every
-    other output is bitwise the same."""
+    """A workspace too small for the parts' sums is accepted. With one slot a
+    tile each tile's parts run in one workgroup: every output bitwise the same.
+    Without room for that either the sweeps run whole: the prompt gradient is
+    the same sum in another fp32 order, every other output bitwise the same."""
     ps, rs, hq, hkv, d = SPLIT[0]
     gi = I.make_inputs(I.custom_shape(ps, rs, hq, hkv, d), seed=950, qk_mult=1.0)
     b, x = GroupBatch.from_shape(gi.shape), upload(gi)
@@ -81,10 +83,59 @@ def test_workspace_without_room_for_the_parts():
     args = (x["q_p"], x["k_p"], x["v_p"], step.o_p, step.lse_p, x["do_p"], x["q_r"], x["k_r"], x["v_r"], step.o_r,
             step.lse_r, x["do_r"])
     full = api.tree_bwd(b, *args, want_f32=True)
-    small = torch.empty(b.workspace_size(api.OP_TREE_BWD) // 2, dtype=torch.uint8, device="cuda")
-    whole = api.tree_bwd(b, *args, want_f32=True, ws=small)
+    buf = lambda n: torch.full((n,), 0xff, dtype=torch.uint8, device="cuda")
+    serial = api.tree_bwd(b, *args, want_f32=True, ws=buf(b.workspace_size(api.OP_TREE_BWD) // 2))
+    whole = api.tree_bwd(b, *args, want_f32=True, ws=buf((b.tp + b.tr) * hq * 4 + 16384))  # D and the schedules
     torch.cuda.synchronize()
+    for k in range(7):
+        assert torch.equal(full[k], serial[k]), k
     for k in (0, 3, 4, 5):
         assert torch.equal(full[k], whole[k]), k
     e = float((full[6].double() - whole[6].double()).norm() / full[6].double().norm())
     assert 0 < e < 1e-5, e   # another order, so not bit for bit
+
+
+def _random_step(ps, rs, hq, hkv, d, seed):
+    b = GroupBatch.from_shape(I.custom_shape(ps, rs, hq, hkv, d))
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    x = {n + "_" + side: torch.randn(t, h, d, generator=gen, device="cuda").to(torch.bfloat16)
+         for side, t in (("p", b.tp), ("r", b.tr)) for n, h in (("q", hq), ("k", hkv), ("v", hkv), ("do", hq))}
+    return b, x
+
+
+# (a tree, how often, an odd one among them, hq, hkv, d): batches that fill the chip
+FULL = [
+    ((150, [500, 800, 911]), 24, None, 8, 2, 128),
+    ((65, [1200, 1033, 900]), 20, (70, [2500] * 5), 4, 2, 64),     # and one tree whose sweeps are longer than the load
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(FULL)))
+def test_parts_in_one_workgroup_match_parts_of_their_own(case):
+    """In a batch that fills the chip the parts of a tile run in one workgroup;
+    alone, each is one of its own: a tree's outputs are bitwise the same."""
+    (p, r), n, odd, hq, hkv, d = FULL[case]
+    ps, rs = [p] * n, [r] * n
+    if odd:
+        ps[5], rs[5] = odd
+    b, x = _random_step(ps, rs, hq, hkv, d, 60 + case)
+    step = SharedStep(b, "cuda")
+    for ws in step.ws.values():
+        ws.fill_(0xff)
+    step.run(x)
+    got = step.outputs()
+    # parts apart alone; one slot a tile in the batch, but for the odd tree
+    size = lambda p, r: GroupBatch.from_shape(I.custom_shape([p], [r], hq, hkv, d)).workspace_size(api.OP_TREE_BWD)
+    assert size(p, r) > 2 * -(-p // 128) * (2 * 128 * hkv * d * 4)
+    assert step.ws["tb"].numel() < (n * size(p, r)) / 1.5 + (size(*odd) if odd else 0)
+    cp, cr = np.concatenate([[0], np.cumsum(ps)]), np.concatenate([[0], np.cumsum([sum(v) for v in rs])])
+    for g in (0, 5, n - 1):
+        ba = GroupBatch.from_shape(I.custom_shape([ps[g]], [rs[g]], hq, hkv, d))
+        rows = {"p": slice(cp[g], cp[g + 1]), "r": slice(cr[g], cr[g + 1])}
+        alone = SharedStep(ba, "cuda")
+        alone.run({k: v[rows[k[-1]]].contiguous() for k, v in x.items()})
+        torch.cuda.synchronize()
+        for k, v in alone.outputs().items():
+            if not k.startswith("lse"):
+                assert torch.equal(got[k][rows[k[-1]]], v), (g, k)

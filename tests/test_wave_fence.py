@@ -3,6 +3,7 @@ LDS. The compiler sees one lane at a time, so each hand-over has to be stated
 as a wavefront fence. In the assembly of this build, after a kernel's last
 workgroup barrier, the writes and the reads of every exchange are separated by
 one, and so are the reads from the writes that follow into the same region."""
+import functools
 import os
 import re
 import subprocess
@@ -12,6 +13,7 @@ import pytest
 from paper_2609_33133_amd import build
 
 
+@functools.lru_cache(None)
 def _assembly(tmp_path, name):
     try:
         cc = build.hipcc()
@@ -46,8 +48,12 @@ def _exchanges(lines):
 @pytest.mark.parametrize("name,kernel,expect", [
     ("attn_fwd.hip", "attn_fwd_kernel", "W|R|"),          # the result tile
     ("attn_bwd.hip", "attn_dq_kernel", "RW|R|W|R|"),      # the key means; the fp32 rows, the bf16 rows
-    ("attn_bwd.hip", "attn_dkv_kernel", "R|W|R|W|R|"),    # the other half's sums; the fp32 rows, the bf16 rows
+    # the other half's sums; the fp32 rows, the bf16 rows (parts in one workgroup: a barrier after the sums)
+    ("attn_bwd.hip", "attn_dkv_kernelILi128ELb0", "R|W|R|W|R|"),
+    ("attn_bwd.hip", "attn_dkv_kernelILi64ELb0", "R|W|R|W|R|"),
+    ("attn_bwd.hip", "attn_dkv_kernelILi128ELb1", "|W|R|W|R|"),
+    ("attn_bwd.hip", "attn_dkv_kernelILi64ELb1", "|W|R|W|R|"),
 ])
-def test_every_exchange_is_fenced(tmp_path, name, kernel, expect):
-    found = {k: _exchanges(v) for k, v in _assembly(tmp_path, name).items() if kernel in k}
+def test_every_exchange_is_fenced(tmp_path_factory, name, kernel, expect):
+    found = {k: _exchanges(v) for k, v in _assembly(tmp_path_factory.getbasetemp(), name).items() if kernel in k}
     assert found and all(v == expect for v in found.values()), found

@@ -295,30 +295,46 @@ void add_replay_qtiles(TileList<QTile>& L, const Shape& s, int bm, int which, co
 }
 
 // Replay forward mode per group (AUGTREE_REPLAY_AUTO). A mode's cost is the
-// number of (query tile, 64-key block) steps its forward tiles execute, at the
-// measured time of one step per workgroup slot of the chip, plus for SPLIT
-// the HBM time of the merge. A fused tile of a short branch sweeps every
-// prompt block for a few rows; the split prompt partial packs the rows of all
-// branches of the group into full tiles, but pays the partials' round trip.
-constexpr double kFwdStepNs = 3.7;         // 128 rows x 64 keys x one head, d = 128, per slot (measured)
+// number of 64-key block steps its forward workgroups execute, at the measured
+// time of one step per workgroup slot of the chip, plus for SPLIT the HBM time
+// of the merge. The split prompt partial packs the rows of all branches of the
+// group into full tiles, but pays the partials' round trip. A tile of r rows
+// has ceil(r g / 128) workgroups with rows, but counts as at least kMinTileShare
+// of the g it is launched as: where most of these end at once, the long ones
+// are unevenly placed over the CUs. Measured with 32 / 8 heads, fused branches
+// of R rows against the split partial with the same number of long workgroups
+// (us): P = 16384, G = 32: R = 32 (one of four) 611 / 312, R = 64 (two) 627 /
+// 512, R = 96 (three) 776 / 789; P = 32768, G = 16: 605 / 535, 611 / 575,
+// 770 / 790. Over 86 shapes (R = 5 .. 4096, five head layouts) the rule's
+// choice takes 1.9 % longer on average than the faster mode, 2.1 % if every
+// tile counts g workgroups, 5.6 % if it counts those with rows only. (The
+// further launches of SPLIT, about 6 us a call, are not priced: they decide only
+// calls of tens of us, P = 2048, G = 16, R = 24 with 28 / 4 heads 39 / 46.)
+constexpr double kFwdStepNs = 3.7;         // 128 pairs x 64 keys, d = 128, per slot (measured)
 constexpr double kMergeBytesPerNs = 5000;  // merge kernel bandwidth (measured, ~5 TB/s)
+constexpr double kMinTileShare = 5.0 / 8;
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 bool replay_prefers_split(const Shape& s, int g, int bm, int bn) {
-  const int64_t prompt_blocks = ceil_div(s.cp[g + 1] - s.cp[g], bn);
-  int64_t fused = 0, own = 0, rows = 0;
+  // workgroups a tile of `rows` rows counts as
+  auto wgs = [&](int64_t rows) {
+    return std::max((double)ceil_div(rows * s.group, kPairsPerWorkgroup), kMinTileShare * s.group);
+  };
+  const double prompt_blocks = (double)ceil_div(s.cp[g + 1] - s.cp[g], bn);
+  double fused = 0, own = 0;
+  int64_t rows = 0;
   for (int b = s.cb[g]; b < s.cb[g + 1]; ++b) {
     const int R = s.cr[b + 1] - s.cr[b];
     rows += R;
     for (int t0 = 0; t0 < R; t0 += bm) {
-      const int64_t own_blocks = ceil_div(std::min(R, t0 + bm), bn);
-      fused += prompt_blocks + own_blocks;
-      own += own_blocks;
+      const double w = wgs(std::min(bm, R - t0)), own_blocks = (double)ceil_div(std::min(R, t0 + bm), bn);
+      fused += w * (prompt_blocks + own_blocks);
+      own += w * own_blocks;
     }
   }
-  const int64_t split = ceil_div(rows, bm) * prompt_blocks + own;
-  const double step = kFwdStepNs * (double)s.d / 128.0 * s.hq;
+  const double split = ((double)(rows / bm) * wgs(bm) + (rows % bm ? wgs(rows % bm) : 0)) * prompt_blocks + own;
+  const double step = kFwdStepNs * (double)s.d / 128.0 * s.hkv;
   const double merge_bytes = (double)rows * s.hq * (10.0 * s.d + 12.0);
   return split * step + merge_bytes / kMergeBytesPerNs < fused * step;
 }

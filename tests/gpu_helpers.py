@@ -4,6 +4,9 @@ and compare with the fp64 oracle at the stated tolerances.
 Tolerances (relative Frobenius error per tensor, LSE max absolute error):
 O <= 1e-2, LSE <= 1e-3, dQ/dK/dV (prompt gradients included) <= 2e-2.
 """
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -18,6 +21,31 @@ TOL_GRAD = 2e-2
 O_KEYS = ("o_p", "o_r")
 LSE_KEYS = ("lse_p", "lse_r")
 GRAD_KEYS = ("dq_p", "dk_p", "dv_p", "dq_r", "dk_r", "dv_r")
+
+
+def inline_tiles() -> int:
+    """Tiles a launch carries in its kernel arguments at most (more are uploaded to the workspace)."""
+    path = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_33133_amd", "csrc",
+                        "kernels.h")
+    return int(re.search(r"constexpr int kInlineTiles = (\d+);", open(path).read()).group(1))
+
+
+def chunks(b: GroupBatch, g: int, chunk_blocks: int) -> int:
+    """Chunks of tree g's prompt-key sweeps (query blocks of 64 rows of one head)."""
+    nr = int(b.cu_resp[b.cu_branch[g + 1]] - b.cu_resp[b.cu_branch[g]])
+    return max(1, min(64, -(-(-(-nr // 64) * (b.hq // b.hkv)) // chunk_blocks)))
+
+
+def query_tiles(b: GroupBatch) -> int:
+    """Tiles of the tree backward's dQ launch."""
+    return int(np.sum(-(-np.diff(b.cu_prompt) // 128)) + np.sum(-(-np.diff(b.cu_resp) // 128)))
+
+
+def key_tiles(b: GroupBatch, chunk_blocks: int = 1024) -> int:
+    """Tiles of the tree backward's dK/dV launch."""
+    n = int(np.sum(-(-np.diff(b.cu_resp) // 128)))
+    return n + sum(-(-int(b.cu_prompt[g + 1] - b.cu_prompt[g]) // 128) * chunks(b, g, chunk_blocks)
+                   for g in range(b.num_groups))
 
 
 def log(msg):

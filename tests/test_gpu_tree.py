@@ -13,7 +13,7 @@ from paper_2609_33133_amd import inputs as I
 from paper_2609_33133_amd.api import REPLAY_AUTO, REPLAY_FUSED, REPLAY_SPLIT, GroupBatch
 from paper_2609_33133_amd.group_attention import SharedStep, upload
 
-from gpu_helpers import assert_close, log, oracle, rel, run_shared
+from gpu_helpers import assert_close, inline_tiles, key_tiles, log, oracle, query_tiles, rel, run_shared
 
 pytestmark = pytest.mark.gpu
 
@@ -29,8 +29,17 @@ CASES = [
     ([300, 70], [[200, 77, 129], [1, 64]], 8, 2, 128, REPLAY_FUSED),
     ([130, 64], [[1, 65], [128, 3, 200]], 4, 4, 64, REPLAY_SPLIT),
     ([700, 130, 256], [[5] * 12, [200, 129], [17] * 4], 8, 2, 128, REPLAY_AUTO),
-    ([1000], [[40] * 24], 28, 4, 128, REPLAY_FUSED),   # > 32 tiles per launch: schedules in the workspace
+    ([1000], [[40] * 24], 28, 4, 128, REPLAY_FUSED),   # 32 tiles per launch; in chunks: schedules in the workspace
+    ([2500, 1800], [[700] * 8, [333] * 11], 4, 1, 64, REPLAY_AUTO),   # every schedule in the workspace
 ]
+
+
+def test_the_last_case_uploads_its_schedules():
+    ps, rs, hq, hkv, d, _ = CASES[-1]
+    b = GroupBatch.from_shape(I.custom_shape(ps, rs, hq, hkv, d))
+    assert min(query_tiles(b), key_tiles(b)) > inline_tiles()
+    b = GroupBatch.from_shape(I.custom_shape(*CASES[3][:5]))
+    assert key_tiles(b) <= inline_tiles() < key_tiles(b, 3)
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))

@@ -37,14 +37,36 @@ def test_split_schedules_on_the_host(tmp_path):
 
 
 # (prompt lens, branch lens, hq, hkv, d): one part edge inside the response rows and one inside the prompt rows,
-# one key tile of one key, a group of seven heads, several trees (schedules in the workspace), a chunked sweep
+# one key tile of one key, a group of seven heads, several trees, cuts in the prompt rows alone, and tiles and items in
+# the workspace (the others' travel in the kernel arguments)
 SPLIT = [
     ([130], [[600, 431, 290]], 8, 2, 128),
     ([1], [[1500]], 8, 1, 64),
     ([700], [[33, 400]], 7, 1, 128),
     ([65, 900], [[1200, 700, 31], [64]], 4, 1, 64),
     ([2100], [[1]], 4, 1, 128),
+    ([2500, 1800], [[700] * 8, [333] * 11], 4, 1, 64),
 ]
+UPLOADED = 5
+
+
+def _batch(case):
+    ps, rs, hq, hkv, d = SPLIT[case]
+    return GroupBatch.from_shape(I.custom_shape(ps, rs, hq, hkv, d))
+
+
+def _scratch(b):
+    """Bytes of the tree backward's workspace beyond D: schedules (under 1 MB), chunks, parts."""
+    return b.workspace_size(api.OP_TREE_BWD) - (b.tp + b.tr) * b.hq * 4
+
+
+@pytest.mark.parametrize("case", range(len(SPLIT)))
+def test_the_cases_are_split(case):
+    from gpu_helpers import inline_tiles, key_tiles
+    b = _batch(case)
+    slot = 2 * 128 * b.hkv * b.d * 4
+    assert _scratch(b) > 2 * slot                                   # parts of their own
+    assert (key_tiles(b) > inline_tiles()) == (case == UPLOADED)
 
 
 @pytest.mark.gpu
@@ -93,6 +115,33 @@ def test_workspace_without_room_for_the_parts():
         assert torch.equal(full[k], whole[k]), k
     e = float((full[6].double() - whole[6].double()).norm() / full[6].double().norm())
     assert 0 < e < 1e-5, e   # another order, so not bit for bit
+
+
+@pytest.mark.gpu
+def test_chunked_and_split():
+    """Prompt-key sweeps that are cut into chunks whose sweeps are split in turn."""
+    from gpu_helpers import assert_close, chunks, oracle, to_np
+    ps, rs, hq, hkv, d = [300], [[2000, 1500, 900]], 8, 1, 64
+    gi = I.make_inputs(I.custom_shape(ps, rs, hq, hkv, d), seed=960, qk_mult=1.0)
+    b, x = GroupBatch.from_shape(gi.shape), upload(gi)
+    plain = _scratch(b)
+    api.set_tree_chunk_blocks(200)
+    try:
+        n = chunks(b, 0, 200)
+        slab = 2 * n * b.tp * hkv * d * 4
+        assert n == 3 and _scratch(b) - slab > plain - (1 << 20)   # (whole chunks: 48 slots of 64 KB less)
+        step = SharedStep(b, "cuda")
+        for ws in step.ws.values():
+            ws.fill_(0xff)
+        step.run(x)
+    finally:
+        api.set_tree_chunk_blocks(0)
+    calls = SharedStep(b, "cuda", path="calls")
+    calls.run(x)
+    torch.cuda.synchronize()
+    assert_close({k: to_np(v) for k, v in step.outputs().items()}, oracle(gi), "chunked and split")
+    for k in ("dq_p", "dq_r", "dk_r", "dv_r"):
+        assert torch.equal(step.outputs()[k], calls.outputs()[k]), k
 
 
 def _random_step(ps, rs, hq, hkv, d, seed):

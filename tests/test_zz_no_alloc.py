@@ -1,9 +1,10 @@
 """The allocation-free backward entry point (augtree_tree_bwd_noalloc,
 through the C ABI): bitwise the outputs of augtree_tree_bwd on two calls in a
 row, the second on a smaller batch (the device array keeps the first call's
-contents); a batch beyond its fixed size rejected on the host; the unchunked
-schedule when the chunks' partials do not fit; and a call captured in a graph
-and replayed."""
+contents); a batch whose schedules are uploaded to the array; parts of split
+sweeps that do not fit in it; a batch beyond its fixed size rejected on the
+host; the unchunked schedule when the chunks' partials do not fit; and a call
+captured in a graph and replayed."""
 import ctypes
 
 import numpy as np
@@ -14,6 +15,8 @@ from paper_2609_33133_amd import _lib, api
 from paper_2609_33133_amd import inputs as I
 from paper_2609_33133_amd.api import GroupBatch
 from paper_2609_33133_amd.group_attention import upload
+
+from gpu_helpers import inline_tiles, key_tiles, query_tiles
 
 pytestmark = pytest.mark.gpu
 
@@ -47,10 +50,26 @@ def _both(shape, seed, f32):
 
 
 def test_noalloc_matches_tree_bwd_on_two_calls():
-    big = I.custom_shape([700, 130, 256], [[5] * 12, [200, 129], [17] * 4], 8, 2, 128)   # > 32 tiles: schedule in the array
+    big = I.custom_shape([700, 130, 256], [[5] * 12, [200, 129], [17] * 4], 8, 2, 128)
     small = I.custom_shape([90], [[65, 40]], 8, 2, 128)
     _both(big, 71, f32=True)
     _both(small, 72, f32=False)
+
+
+def test_noalloc_with_schedules_in_the_array():
+    """Tiles of both launches, and the items of split sweeps, uploaded to the array."""
+    shape = I.custom_shape([2500, 1800], [[700] * 8, [333] * 11], 4, 1, 64)
+    b = GroupBatch.from_shape(shape)
+    assert min(query_tiles(b), key_tiles(b)) > inline_tiles()
+    assert b.workspace_size(api.OP_TREE_BWD) < _lib.load().augtree_noalloc_scratch_bytes()
+    _both(shape, 75, f32=True)
+
+
+def test_noalloc_runs_the_parts_in_one_workgroup_when_they_do_not_fit():
+    """The parts of these eight trees' sweeps take more than the 64 MiB array; one slot a tile fits: the same bits."""
+    shape = I.custom_shape([400] * 8, [[500] * 8] * 8, 8, 2, 128)
+    assert GroupBatch.from_shape(shape).workspace_size(api.OP_TREE_BWD) > _lib.load().augtree_noalloc_scratch_bytes()
+    _both(shape, 76, f32=True)
 
 
 def test_noalloc_rejects_batches_beyond_its_array():

@@ -42,10 +42,11 @@
  *   from prefill_fwd until prefill_bwd.
  * Outputs are overwritten, never accumulated into.
  * Workspace: `ws` must hold augtree_workspace_size(...) bytes (256-byte
- *   aligned). A launch of more than a few dozen tiles reads its tile schedule
- *   from the workspace, written there with an asynchronous host-to-device copy
- *   on `stream` (the host staging happens before the call returns); smaller
- *   schedules travel in the kernel arguments. The backward also keeps
+ *   aligned). A launch of more than 112 tiles of 128 rows (35 where sweeps are
+ *   split) may read its tile schedule from the workspace, written there with
+ *   an asynchronous host-to-device copy on `stream` (the host staging happens
+ *   before the call returns); smaller schedules travel in the kernel
+ *   arguments. The backward also keeps
  *   D = rowsum(dO * O) of every row there (written by its dQ kernel, read by
  *   its dK/dV kernel), and the fp32 sums of key tiles whose sweep is split
  *   into parts (trees with few key tiles and long sweeps): of each part where
@@ -65,7 +66,11 @@
  *   and a tree's outputs do not depend on the other trees of the batch (each
  *   output element is computed by one workgroup in a fixed order, or as parts
  *   whose cuts follow from the tree alone and which are added in a fixed
- *   order, whatever order the tiles are scheduled in).
+ *   order, whatever order the tiles are scheduled in). The second holds for
+ *   workspaces of augtree_workspace_size() bytes or more: a smaller one, or the
+ *   fixed array of augtree_tree_bwd_noalloc, may have no room for a batch's
+ *   parts or chunks, and the whole sweeps that then run round the key
+ *   gradients of its trees differently.
  * Thread safety: calls are reentrant; calls on different streams that share a
  *   workspace race.
  */
@@ -306,17 +311,17 @@ int augtree_tree_bwd(const augtree_groups* grp, const uint16_t* q_p, const uint1
  * augtree_tree_bwd (bit for bit, except that a batch whose split sweeps do not
  * fit the array even with one slot a tile runs them whole, and one whose
  * chunks do not fit runs one sweep per prompt-key tile: the same gradients up
- * to fp32 summation order). Its workspace is a fixed 64 MiB device array of the library (augtree_noalloc_scratch_bytes()),
- * one copy per GPU, held from the first call on that GPU until the process
- * ends; the call performs no allocation. A batch whose unchunked workspace
- * exceeds it is rejected with AUGTREE_ERR_WORKSPACE before anything is
- * enqueued. Calls that overlap on
- * one GPU (several streams or threads) share the array and race; serialise
- * them. Stream capture: a launch whose tile schedule has more than 32 tiles
- * (and a chunked batch's row map) may receive it by a host-to-device copy from
- * a host buffer the call frees on return, so a graph captured around such a
- * call must not be replayed; batches of at most 32 tiles per launch and no
- * chunks enqueue kernels only (schedules in the kernel arguments).
+ * to fp32 summation order). Its workspace is a fixed 64 MiB device array of
+ * the library (augtree_noalloc_scratch_bytes()), one copy per GPU, held from
+ * the first call on that GPU until the process ends; the call performs no
+ * allocation. A batch whose workspace without chunks and splits exceeds it is
+ * rejected with AUGTREE_ERR_WORKSPACE before anything is enqueued. Calls that
+ * overlap on one GPU (several streams or threads) share the array and race;
+ * serialise them. Stream capture: a schedule that does not fit the kernel arguments, and
+ * a chunked batch's row map, come by a host-to-device copy from a host buffer
+ * the call frees on return, so a graph captured around such a call must not be
+ * replayed. Batches without chunks of at most 112 tiles per launch (128 query
+ * or key rows each), or 35 where sweeps are split, enqueue kernels only.
  */
 int augtree_tree_bwd_noalloc(const augtree_groups* grp, const uint16_t* q_p, const uint16_t* k_p,
                              const uint16_t* v_p, const uint16_t* o_p, const float* lse_p,

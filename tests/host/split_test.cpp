@@ -62,6 +62,7 @@ hipError_t launch_grad_reduce(int, int64_t, int64_t, const float*, int, int64_t,
 hipError_t launch_attn_dkv(const DkvParams& p, int n, hipStream_t) {
   const KVTile* tiles = p.tiles ? p.tiles : p.inl;
   CHECK(p.tiles || n <= kInlineTiles);
+  CHECK(n > (p.n_items ? 35 : 112) || (!p.tiles && !p.items));  // what augtree.h says of the kernel arguments
   g_parts.assign(n, 1);
   auto note_cuts = [&] {
     g_cuts.clear();

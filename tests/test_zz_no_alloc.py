@@ -72,6 +72,41 @@ def test_noalloc_runs_the_parts_in_one_workgroup_when_they_do_not_fit():
     _both(shape, 76, f32=True)
 
 
+def test_noalloc_runs_whole_sweeps_without_a_slot_a_tile():
+    """72 split tiles of 1 MiB a slot: the array has no room for either form of
+    the parts, so these sweeps run whole. This is where a tree's rounding
+    depends on the batch: the same tree alone keeps its parts. dQ and the
+    branch-key gradients are bitwise those of augtree_tree_bwd, the prompt-key
+    gradient the same sum in another fp32 order."""
+    n, p, g, r, hq, hkv, d = 36, 150, 16, 256, 16, 8, 128
+    b = GroupBatch.from_shape(I.custom_shape([p] * n, [[r] * g] * n, hq, hkv, d))
+    gen = torch.Generator(device="cuda").manual_seed(77)
+    mk = lambda t, h: torch.randn(t, h, d, generator=gen, device="cuda").to(torch.bfloat16)
+    qp, dop, qr, dor = mk(b.tp, hq), mk(b.tp, hq), mk(b.tr, hq), mk(b.tr, hq)
+    kp, vp, kr, vr = mk(b.tp, hkv), mk(b.tp, hkv), mk(b.tr, hkv), mk(b.tr, hkv)
+    o_p, lse_p, o_r, lse_r, _, _ = api.tree_fwd(b, qp, kp, vp, qr, kr, vr)
+    args = (qp, kp, vp, o_p, lse_p, dop, qr, kr, vr, o_r, lse_r, dor)
+    ref = api.tree_bwd(b, *args, want_f32=True)
+    outs, f32 = [torch.full_like(t, 7) for t in ref[:6]], torch.full_like(ref[6], 7)
+    _lib.check(_run_noalloc(b, args, outs, f32), "tree_bwd_noalloc")
+    # the first tree alone
+    ba = GroupBatch.from_shape(I.custom_shape([p], [[r] * g], hq, hkv, d))
+    lse = lambda t, k: t[:, :k].contiguous()
+    k = r * g
+    alone = (qp[:p], kp[:p], vp[:p], o_p[:p], lse(lse_p, p), dop[:p], qr[:k], kr[:k], vr[:k], o_r[:k], lse(lse_r, k),
+             dor[:k])
+    outs1 = [torch.full((t, h, d), 7, dtype=torch.bfloat16, device="cuda")
+             for t, h in ((p, hq), (p, hkv), (p, hkv), (k, hq), (k, hkv), (k, hkv))]
+    f32_1 = torch.full((2, p, hkv, d), 7.0, device="cuda")
+    _lib.check(_run_noalloc(ba, alone, outs1, f32_1), "tree_bwd_noalloc (alone)")
+    torch.cuda.synchronize()
+    for i in (0, 3, 4, 5):
+        assert torch.equal(outs[i], ref[i]), NAMES[i]
+    assert torch.equal(f32_1, ref[6][:, :p])          # the parts in either form, alone or not
+    e = float((f32.double() - ref[6].double()).norm() / ref[6].double().norm())
+    assert 0 < e < 1e-5, e                            # whole sweeps
+
+
 def test_noalloc_rejects_batches_beyond_its_array():
     lib = _lib.load()
     cap = lib.augtree_noalloc_scratch_bytes()

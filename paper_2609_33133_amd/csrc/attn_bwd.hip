@@ -729,11 +729,12 @@ __global__ __launch_bounds__(512) void attn_dkv_kernel(DkvParams p) {
 // Adds the partial sums of the split tiles in part order and writes the tile's
 // outputs, as the dK/dV kernel does for an unsplit tile. One thread adds four
 // consecutive accumulator registers of one lane: the four keys
-// 32 kq + acc_row(4 g4 .. 4 g4 + 3, hf) of column 32 db + l32. Bound by HBM:
-// 92 MB read and written in 18 us (5.2 TB/s). (Adding them in the part that
-// finishes last, found with a counter, instead: the device-scope fences write
-// back and invalidate the XCD's L2 under the running parts, and the dK/dV
-// launch of three small trees took 189 us against 131 us for both kernels.)
+// 32 kq + acc_row(4 g4 .. 4 g4 + 3, hf) of column 32 db + l32. Bound by memory:
+// three trees of P = 384 .. 1337 with 8 / 2 heads, 47 MB of parts, 9.2 us (5.1
+// TB/s). (Adding them in the part that finishes last, found with a counter,
+// instead: the device-scope fences write back and invalidate the XCD's L2 under
+// the running parts, and the dK/dV launch of these trees took 189 us against
+// 131 us for both kernels.)
 constexpr int COMBINE_THREADS = 256;
 
 template <int D>
